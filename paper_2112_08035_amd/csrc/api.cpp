@@ -796,6 +796,30 @@ static smcrt_status pack_accel(const smcrt_scene* s, SceneHeader* h, const std::
   return SMCRT_OK;
 }
 
+template <typename T>
+static void pack_steps(const smcrt_scene* s, const SceneHeader* h, const Prim<T>* prims, StepRec<T>* out) {
+  for (int r = 0; r < h->n_regions; ++r) {
+    const Region& R = h->reg[r];
+    if (r == s->accel_region) {
+      out->bits = kStepAccel | kStepFirst | kStepLast;
+      out->index = R.first;
+      ++out;
+      continue;
+    }
+    for (int i = 0; i < R.count; ++i, ++out) {
+      const Prim<T>& P = prims[R.first + i];
+      out->bits = (P.kind & kStepKind) | (i == 0 ? kStepFirst : 0) | (i + 1 == R.count ? kStepLast : 0) |
+                  (P.flags ? kStepPlaced : 0) | (R.op << kStepOp);
+      out->index = R.first + i;
+      std::memcpy(out->v, P.v, sizeof(out->v));
+      out->k = (T)R.k;
+      out->inv_k = (T)R.inv_k;
+    }
+  }
+}
+
+static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+
 static smcrt_status pack(smcrt_scene* s) {
   if (!s->dirty) return SMCRT_OK;
   smcrt_status st = check_complete(s);
@@ -825,6 +849,13 @@ static smcrt_status pack(smcrt_scene* s) {
       bytes = cap_f + n_caps * 8 * sizeof(float);
     }
   }
+  // evaluation records: one per primitive, one for the accelerated region
+  const bool grid = s->accel_region >= 0 && s->accel_region < (int)s->regions.size();
+  const size_t n_steps = grid ? np - s->regions[s->accel_region].prims.size() + 1 : np;
+  const size_t step_d = align256(bytes);
+  const size_t step_f = align256(step_d + n_steps * sizeof(StepRec<double>));
+  const size_t table_bytes = bytes;
+  bytes = step_f + n_steps * sizeof(StepRec<float>);
   s->blob.assign(bytes, 0);
   SceneHeader* h = reinterpret_cast<SceneHeader*>(s->blob.data());
   PrimD* pd = reinterpret_cast<PrimD*>(s->blob.data() + off_d);
@@ -842,6 +873,11 @@ static smcrt_status pack(smcrt_scene* s) {
     h->reg[r].seg = s->segment ? seg_rule(s, hr) : kSegNone;
     first += (int)hr.prims.size();
   }
+  pack_steps(s, h, pd, reinterpret_cast<StepRec<double>*>(s->blob.data() + step_d));
+  pack_steps(s, h, pf, reinterpret_cast<StepRec<float>*>(s->blob.data() + step_f));
+  h->n_steps = (int32_t)n_steps;
+  h->step_offset_d = step_d;
+  h->step_offset_f = step_f;
   fill_region(h->reg[s->regions.size()], 0.0, 0.0, 0.0, s->n_ambient, 0.0, kUnion, 0, 0);
   h->delta = s->delta;
   h->deltaf = (float)s->delta;
@@ -954,6 +990,7 @@ static smcrt_status pack(smcrt_scene* s) {
   h->prim_offset_d = off_d;
   h->prim_offset_f = off_f;
   h->blob_bytes = bytes;
+  h->table_bytes = table_bytes;
   s->dirty = false;
   return SMCRT_OK;
 }
@@ -1111,6 +1148,20 @@ static LaunchCfg launch_cfg(smcrt_engine* e, int launch_class) {
   return c;
 }
 
+// Lanes of each wave that take packets, for a launch of cfg over n packets:
+// all of them when there are packets for every lane, else the packets are
+// spread over all waves.  A short launch ends with its longest packet, and a
+// wave's iteration is as long as the paths of all its lanes together: 1e3
+// packets of the 50^3 sphere take 2.1 ms one to a wave and 3.6 ms in 16 full
+// waves, 1e5 packets 7.3 ms against 7.9 ms.  A quarter of these lanes (so
+// that most waves' lanes are refilled four times) was 8 % slower on 5e5
+// packets of a vessel network, twice as many the same to 7 % slower.
+static int32_t packet_lanes(const LaunchCfg& cfg, uint64_t n) {
+  const uint64_t waves = (uint64_t)cfg.grid * (uint64_t)(cfg.block / 64);
+  const uint64_t each = n / waves + (n % waves != 0);
+  return (int32_t)std::min<uint64_t>(64, std::max<uint64_t>(1, each));
+}
+
 struct JobSpec {
   smcrt_scene* s;
   uint64_t seed, first, n;
@@ -1136,8 +1187,6 @@ struct DistSpec {
   int32_t* owner;
   double* normals;
 };
-
-static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Lays the jobs' scenes, the job table, the per-job counters, the uniform
 // grids and the voxel grids out in the engine arena, uploads the tables,
@@ -1222,6 +1271,8 @@ static smcrt_status launch_jobs(smcrt_engine* e, const std::vector<JobSpec>& job
     a.sc = reinterpret_cast<const SceneHeader*>(sc);
     a.pd = reinterpret_cast<const PrimD*>(sc + h->prim_offset_d);
     a.pf = reinterpret_cast<const PrimF*>(sc + h->prim_offset_f);
+    a.step_d = reinterpret_cast<const StepRec<double>*>(sc + h->step_offset_d);
+    a.step_f = reinterpret_cast<const StepRec<float>*>(sc + h->step_offset_f);
     a.seed = jobs[j].seed;
     a.first = jobs[j].first;
     a.n = jobs[j].n;
@@ -1257,6 +1308,16 @@ static smcrt_status launch_jobs(smcrt_engine* e, const std::vector<JobSpec>& job
       a.detector = nullptr;
     }
   }
+  bool has_geom[kLaunchClasses] = {};
+  uint64_t class_packets[kLaunchClasses] = {};
+  for (size_t j = 0; j < jobs.size(); ++j) {
+    const int g = table[j].geometry;
+    has_geom[g] = true;
+    class_packets[g] += std::min(jobs[j].n, UINT64_MAX - class_packets[g]);
+  }
+  LaunchCfg cg[kLaunchClasses];
+  for (int g = 0; g < kLaunchClasses; ++g) cg[g] = launch_cfg(e, g);
+  for (size_t j = 0; j < jobs.size(); ++j) table[j].lanes = packet_lanes(cg[table[j].geometry], class_packets[table[j].geometry]);
   // upload through pinned staging; wait until the previous upload left it
   if (e->stage_pending) {
     HIP_TRY(hipEventSynchronize(e->stage_done), "hipEventSynchronize(stage)");
@@ -1280,10 +1341,6 @@ static smcrt_status launch_jobs(smcrt_engine* e, const std::vector<JobSpec>& job
   B.n_jobs = (int32_t)jobs.size();
   B.refill_min = e->opts.refill_min;
   B.surface_min = e->opts.surface_min;
-  bool has_geom[kLaunchClasses] = {};
-  for (size_t j = 0; j < jobs.size(); ++j) has_geom[table[j].geometry] = true;
-  LaunchCfg cg[kLaunchClasses];
-  for (int g = 0; g < kLaunchClasses; ++g) cg[g] = launch_cfg(e, g);
   if (tr) {
     for (LaunchCfg& c : cg) {
       c.block = 64;
@@ -1438,9 +1495,11 @@ extern "C" smcrt_status smcrt_run_ex_static(smcrt_engine* e, const smcrt_scene* 
     vox_off = off;
     off = align256(off + vox_n);
   }
-  if (off > kStaticScratchBytes)
+  // (the evaluation records have room of their own)
+  const size_t need = off - (align256(s->blob.size()) - align256(h->table_bytes));
+  if (need > kStaticScratchBytes)
     return fail(SMCRT_E_INVALID, "run_ex_static: the scene needs %zu bytes of device scratch, the static scratch holds %zu",
-                off, kStaticScratchBytes);
+                need, kStaticScratchBytes);
   HIP_TRY(hipSetDevice(e->device), "hipSetDevice");
   void* base_v = nullptr;
   HIP_TRY(static_scratch(e->device, &base_v), "static scratch address");
@@ -1451,6 +1510,8 @@ extern "C" smcrt_status smcrt_run_ex_static(smcrt_engine* e, const smcrt_scene* 
   a.sc = reinterpret_cast<const SceneHeader*>(base);
   a.pd = reinterpret_cast<const PrimD*>(base + h->prim_offset_d);
   a.pf = reinterpret_cast<const PrimF*>(base + h->prim_offset_f);
+  a.step_d = reinterpret_cast<const StepRec<double>*>(base + h->step_offset_d);
+  a.step_f = reinterpret_cast<const StepRec<float>*>(base + h->step_offset_f);
   a.seed = seed;
   a.first = first_packet;
   a.n = n_packets;
@@ -1461,6 +1522,8 @@ extern "C" smcrt_status smcrt_run_ex_static(smcrt_engine* e, const smcrt_scene* 
   a.tallies = out->tallies;
   a.acc_region = h->acc.region;
   a.geometry = job_class(e->opts, h, false);
+  const LaunchCfg cfg = launch_cfg(e, a.geometry);
+  a.lanes = packet_lanes(cfg, n_packets);
   if (h->acc.region >= 0 && h->acc.caps) {
     a.acc_capd = reinterpret_cast<const double*>(base + h->acc.cap_offset_d);
     a.acc_capf = reinterpret_cast<const float*>(base + h->acc.cap_offset_f);
@@ -1489,7 +1552,7 @@ extern "C" smcrt_status smcrt_run_ex_static(smcrt_engine* e, const smcrt_scene* 
   B.refill_min = e->opts.refill_min;
   B.surface_min = e->opts.surface_min;
   B.geometry = a.geometry;
-  HIP_TRY(launch_walk(e->opts.precision, false, launch_cfg(e, a.geometry), B, q), "walk kernel");
+  HIP_TRY(launch_walk(e->opts.precision, false, cfg, B, q), "walk kernel");
   return SMCRT_OK;
 }
 
@@ -1779,10 +1842,11 @@ static double server_now(const smcrt_server* sv) {
 
 // device bytes a request holds while admitted: its outputs, its scene
 // tables, the grid buffers of its accelerated region and its voxel grid
-// (served requests tally straight into their output grid: no brick grid)
+// (served requests tally straight into their output grid: no brick grid).
+// The walk's evaluation records are not charged to it.
 static uint64_t request_footprint(const smcrt_scene* s) {
   const SceneHeader* h = reinterpret_cast<const SceneHeader*>(s->blob.data());
-  uint64_t b = s->blob.size() + sizeof(WalkArgs) + sizeof(smcrt_tallies) + 8 * kMaxRegions + 256;
+  uint64_t b = h->table_bytes + sizeof(WalkArgs) - 2 * sizeof(void*) + sizeof(smcrt_tallies) + 8 * kMaxRegions + 256;
   if (h->has_grid) b += 8ull * h->g_dims[0] * h->g_dims[1] * h->g_dims[2];
   if (h->acc.region >= 0) b += 12ull * ((uint64_t)h->acc.n_cells + 1) + 4ull * h->acc.capacity + 3 * 256;
   if (h->geometry == kGeomVoxel) b += (uint64_t)h->g_dims[0] * h->g_dims[1] * h->g_dims[2] + 256;
@@ -1971,6 +2035,7 @@ static void resident_job(smcrt_server* sv, int s, WalkArgs& a) {
   a.counter = R->d_counters + s;
   a.resume_next = R->d_resume_next + s;
   a.slot = s;
+  a.lanes = 64;
   a.geometry = -1;  // in no launch class
   if (!sl.r) return;
   const Request* r = sl.r;
@@ -1978,6 +2043,8 @@ static void resident_job(smcrt_server* sv, int s, WalkArgs& a) {
   a.sc = reinterpret_cast<const SceneHeader*>(sl.dev);
   a.pd = reinterpret_cast<const PrimD*>(sl.dev + h->prim_offset_d);
   a.pf = reinterpret_cast<const PrimF*>(sl.dev + h->prim_offset_f);
+  a.step_d = reinterpret_cast<const StepRec<double>*>(sl.dev + h->step_offset_d);
+  a.step_f = reinterpret_cast<const StepRec<float>*>(sl.dev + h->step_offset_f);
   a.seed = r->seed;
   a.first = 0;
   a.n = r->cancel ? std::min(sl.handed, r->n) : r->n;  // a cancelled request takes no new ids

@@ -49,6 +49,11 @@ hipError_t launch_zero_u32(unsigned int* p, int n, hipStream_t stream);
 // its size, and its address on `device`, which must be the current device
 // (looked up once per device and kept).
 constexpr size_t kStaticScratchBytes = size_t(32) << 20;
+// beside it, room for the evaluation records of any scene whose other tables
+// fit: a primitive's records take less than 3/8 of its Prim records
+constexpr size_t kStaticStepBytes = size_t(12) << 20;
+static_assert(8 * (sizeof(StepRec<double>) + sizeof(StepRec<float>)) <= 3 * (sizeof(PrimD) + sizeof(PrimF)) &&
+              8 * (kStaticStepBytes - 4096) >= 3 * kStaticScratchBytes - 8 * 4096, "evaluation records fit");
 hipError_t static_scratch(int device, void** out);
 // *dst = a, with a passed as a kernel argument
 hipError_t launch_write_job(const WalkArgs& a, WalkArgs* dst, hipStream_t stream);

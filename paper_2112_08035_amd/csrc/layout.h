@@ -2,7 +2,8 @@
 //
 // One contiguous blob per scene: a SceneHeader, then n_prims PrimD (FP64
 // parameters, used by the interface step and by FP64 transport), then
-// n_prims PrimF (FP32 copies for FP32 transport).  Every table is read with
+// n_prims PrimF (FP32 copies for FP32 transport), then the evaluation records
+// of the walk's steps in both precisions.  Every table is read with
 // wave-uniform indices, so the kernels fetch it through the scalar cache into
 // SGPRs; nothing per lane.
 #pragma once
@@ -78,6 +79,28 @@ struct Prim {
 };
 using PrimD = Prim<double>;
 using PrimF = Prim<float>;
+
+// One step of the walk's distance evaluation: a primitive of a region, or the
+// whole of the accelerated region.  The records of a scene follow each other
+// in region order, each in whole cache lines, so a walk reads the next one
+// while it works on this one, and needs no other table to know what to do.
+enum StepBits : int32_t {
+  kStepKind = 15,     // PrimKind, or kStepAccel
+  kStepAccel = 15,    // the accelerated region, through its grid
+  kStepFirst = 16,    // first record of its region
+  kStepLast = 32,     // last record of its region
+  kStepPlaced = 64,   // placed or modified: evaluated from its Prim record
+  kStepOp = 8         // shift of the region's RegionOp
+};
+template <typename T>
+struct StepRec {
+  int32_t bits;
+  int32_t index;  // primitive (region order)
+  T v[10];        // Prim::v
+  T k, inv_k;     // smooth-union radius
+  int32_t pad[sizeof(T) == 4 ? 2 : 6];
+};
+static_assert(sizeof(StepRec<float>) == 64 && sizeof(StepRec<double>) == 128, "whole cache lines");
 
 struct Region {
   int32_t first, count, op;       // primitive range (region order) and CSG op
@@ -158,7 +181,9 @@ struct SceneHeader {
   Region reg[kMaxRegions + 1];
   Accel acc;
   uint64_t prim_offset_d, prim_offset_f;  // byte offsets of the tables in the blob
-  uint64_t blob_bytes;
+  uint64_t step_offset_d, step_offset_f;  // StepRec tables, n_steps records, the blob's last part
+  int32_t n_steps, pad_steps;
+  uint64_t blob_bytes, table_bytes;       // the blob, and the blob without the StepRec tables
 };
 
 // Launch configuration chosen by the host.
@@ -190,7 +215,10 @@ struct WalkArgs {
   int32_t n_trace, max_records;
   int32_t acc_region;            // copy of sc->acc.region (-1 = none)
   int32_t geometry;              // launch class: sc->geometry, plus kLaunchXf when sc->xf
-  int32_t brick, pad_brick;      // 1: fluence is the 2x2x2-brick scratch grid (brick_index)
+  int32_t brick;                 // 1: fluence is the 2x2x2-brick scratch grid (brick_index)
+  int32_t lanes;                 // lanes of each wave that take this job's packets (1..64)
+  const StepRec<double>* step_d; // evaluation records, sc->n_steps of them
+  const StepRec<float>* step_f;
   const double* acc_capd;        // compact capsule records of the accelerated region
   const float* acc_capf;         //   (8 values each), or null when acc.caps = 0
   // resident serving: packets of this job saved at the end of the previous

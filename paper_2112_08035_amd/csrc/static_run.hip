@@ -12,7 +12,7 @@
 
 namespace smcrt {
 
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticStepBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;

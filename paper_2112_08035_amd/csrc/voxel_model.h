@@ -48,9 +48,8 @@ __device__ __forceinline__ void escape_face(JobRef a, Packet<T>& pk, Lane& ln, L
 // region r2 (n_regions = ambient).  FP64 Fresnel with the axis as normal.
 // Returns true when the packet passed into r2, false when it reflected.
 template <typename T, bool TRACE>
-__device__ bool voxel_interface(JobRef a, Packet<T>& pk, Lane& ln, LdsTallies& L, int ax, int r2, double n1,
+__device__ bool voxel_interface(JobRef a, Regions<T> rg, Packet<T>& pk, Lane& ln, LdsTallies& L, int ax, int r2, double n1,
                                 double n2) {
-  ScP sc = kptr(a.sc);
   pk.k += 1;
   pk.steps = 0;
   atomicAdd(&L.cnt[kCInterfaces], 1ull);
@@ -72,7 +71,7 @@ __device__ bool voxel_interface(JobRef a, Packet<T>& pk, Lane& ln, LdsTallies& L
   set_comp(u, ax, comp(u, ax) + (ct - eta * ci) * sg);
   u = (1.0 / __builtin_sqrt(dot(u, u))) * u;
   pk.u = from_d<T>(u);
-  set_region(sc, pk, r2);
+  set_region(rg, pk, r2);
   atomicAdd(&L.cnt[kCRefractions], 1ull);
   record<T, TRACE>(a, pk, ln, SMCRT_EV_REFRACT);
   return true;
@@ -82,7 +81,7 @@ __device__ bool voxel_interface(JobRef a, Packet<T>& pk, Lane& ln, LdsTallies& L
 // outside if it was born there.  Returns false when the packet has ended
 // (it missed the grid, or reflected off the grid face it arrived at).
 template <typename T, bool TRACE>
-__device__ bool enter_grid(JobRef a, Packet<T>& pk, int v[3], Lane& ln, LdsTallies& L) {
+__device__ bool enter_grid(JobRef a, Regions<T> rg, Packet<T>& pk, int v[3], Lane& ln, LdsTallies& L) {
   ScP sc = kptr(a.sc);
   const int nr = sc->n_regions;
   const V3<T> p = pk.p, u = pk.u;
@@ -124,7 +123,7 @@ __device__ bool enter_grid(JobRef a, Packet<T>& pk, int v[3], Lane& ln, LdsTalli
       return false;
     }
     shift(pk, t0);
-    set_region(sc, pk, nr);  // in the ambient medium, on the grid face
+    set_region(rg, pk, nr);  // in the ambient medium, on the grid face
   }
   // voxel holding the point; on a voxel face, the one the packet moves into
 #pragma unroll
@@ -139,15 +138,15 @@ __device__ bool enter_grid(JobRef a, Packet<T>& pk, int v[3], Lane& ln, LdsTalli
   }
   const int r2 = a.vox[vox_index(sc, v)];
   if (entry < 0) {
-    set_region(sc, pk, r2);
+    set_region(rg, pk, r2);
     return true;
   }
-  const double n1 = sc->reg[nr].n, n2 = sc->reg[r2].n;
+  const double n1 = rg[nr].n, n2 = rg[r2].n;
   if (n1 == n2) {
-    set_region(sc, pk, r2);
+    set_region(rg, pk, r2);
     return true;
   }
-  if (voxel_interface<T, TRACE>(a, pk, ln, L, entry, r2, n1, n2)) return true;
+  if (voxel_interface<T, TRACE>(a, rg, pk, ln, L, entry, r2, n1, n2)) return true;
   // reflected off the grid: it leaves through the face it came to
   escape_face<T, TRACE>(a, pk, ln, L, 2 * entry + (comp(pk.u, entry) > T(0) ? 1 : 0), true);
   return false;
@@ -158,7 +157,7 @@ __device__ bool enter_grid(JobRef a, Packet<T>& pk, int v[3], Lane& ln, LdsTalli
 // pk.state = kInteract when the optical depth runs out.  Returns false when
 // the packet has ended (escape or step cap).
 template <typename T, bool TRACE>
-__device__ bool voxel_step(JobRef a, Packet<T>& pk, int v[3], Lane& ln, LdsTallies& L, int max_steps,
+__device__ bool voxel_step(JobRef a, Regions<T> rg, Packet<T>& pk, int v[3], Lane& ln, LdsTallies& L, int max_steps,
                            uint32_t max_events) {
   ScP sc = kptr(a.sc);
   if (++pk.steps > max_steps || pk.k > max_events) {
@@ -200,17 +199,17 @@ __device__ bool voxel_step(JobRef a, Packet<T>& pk, int v[3], Lane& ln, LdsTalli
   const int face = 2 * ax + (ua > T(0) ? 1 : 0);
   const bool off = w2[ax] < 0 || w2[ax] >= sc->g_dims[ax];
   const int r2 = off ? sc->n_regions : (int)a.vox[vox_index(sc, w2)];
-  const double n1 = sc->reg[pk.region].n, n2 = sc->reg[r2].n;
+  const double n1 = rg[pk.region].n, n2 = rg[r2].n;
   if (n1 == n2) {
     if (off) {
       escape_face<T, TRACE>(a, pk, ln, L, face, true);
       return false;
     }
     v[0] = w2[0]; v[1] = w2[1]; v[2] = w2[2];
-    if (r2 != pk.region) set_region(sc, pk, r2);
+    if (r2 != pk.region) set_region(rg, pk, r2);
     return true;
   }
-  if (!voxel_interface<T, TRACE>(a, pk, ln, L, ax, r2, n1, n2)) return true;  // reflected: same voxel
+  if (!voxel_interface<T, TRACE>(a, rg, pk, ln, L, ax, r2, n1, n2)) return true;  // reflected: same voxel
   if (off) {  // transmitted out of the grid
     atomicAdd(&L.escaped[face], pk.w);
     atomicAdd(&L.cnt[kCEscapes], 1ull);

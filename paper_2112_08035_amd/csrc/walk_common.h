@@ -24,6 +24,19 @@ __device__ __forceinline__ const SMCRT_K X* kptr(const X* p) {
   return (const SMCRT_K X*)p;
 }
 
+// The same pointer, opaque to the compiler.  Table values read through it are
+// read where they are used: read through the plain pointer, the compiler moves
+// the loads of all of them to the start of the job, runs out of scalar
+// registers and fetches them back from vector lanes one by one.
+template <class X>
+__device__ __forceinline__ const SMCRT_K X* fresh(const SMCRT_K X* p) {
+  uint64_t v = (uint64_t)p;
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+s"(v));
+#endif
+  return (const SMCRT_K X*)v;
+}
+
 // ------------------------------------------------------------------ types
 
 template <typename T>
@@ -127,6 +140,10 @@ template <>
 struct Tab<float> {
   static __device__ __forceinline__ const SMCRT_K PrimF* prims(JobRef a) { return kptr(a.pf); }
   static __device__ __forceinline__ const SMCRT_K float* caps(JobRef a) { return kptr(a.acc_capf); }
+  static __device__ __forceinline__ const SMCRT_K StepRec<float>* steps(JobRef a) { return kptr(a.step_f); }
+  static __device__ __forceinline__ float hg_b(RegRef r) { return r.hg_bf; }
+  static __device__ __forceinline__ float hg_c(RegRef r) { return r.hg_cf; }
+  static __device__ __forceinline__ float hg_d(RegRef r) { return r.hg_df; }
   static __device__ __forceinline__ float k(RegRef r) { return r.kf; }
   static __device__ __forceinline__ float inv_k(RegRef r) { return r.inv_kf; }
   static __device__ __forceinline__ float mut(RegRef r) { return r.mutf; }
@@ -159,6 +176,10 @@ template <>
 struct Tab<double> {
   static __device__ __forceinline__ const SMCRT_K PrimD* prims(JobRef a) { return kptr(a.pd); }
   static __device__ __forceinline__ const SMCRT_K double* caps(JobRef a) { return kptr(a.acc_capd); }
+  static __device__ __forceinline__ const SMCRT_K StepRec<double>* steps(JobRef a) { return kptr(a.step_d); }
+  static __device__ __forceinline__ double hg_b(RegRef r) { return r.hg_b; }
+  static __device__ __forceinline__ double hg_c(RegRef r) { return r.hg_c; }
+  static __device__ __forceinline__ double hg_d(RegRef r) { return r.hg_d; }
   static __device__ __forceinline__ double k(RegRef r) { return r.k; }
   static __device__ __forceinline__ double inv_k(RegRef r) { return r.inv_k; }
   static __device__ __forceinline__ double mut(RegRef r) { return r.mut; }
@@ -187,12 +208,15 @@ struct Tab<double> {
   static __device__ __forceinline__ double seg_eps() { return 1e-12; }
 };
 
+// x^2 + y^2 with its one rounding fixed in FP32 (which product the compiler
+// would fuse depends on the code around it; results do not)
+__device__ __forceinline__ float sum_sq(float x, float y) { return __builtin_fmaf(x, x, y * y); }
+__device__ __forceinline__ double sum_sq(double x, double y) { return x * x + y * y; }
+
 // exact Euclidean SDF of one primitive's shape in its own frame (Sec. 2.2;
 // Eq. 3 for the sphere)
-template <typename T>
-__device__ __forceinline__ T shape_sdf(const SMCRT_K Prim<T>* P, int i, V3<T> p) {
-  const int kind = P[i].kind;
-  const SMCRT_K T* v = P[i].v;
+template <typename T, typename Params>
+__device__ __forceinline__ T shape_of(int kind, const Params& v, V3<T> p) {
   const V3<T> q = p - mk(v[0], v[1], v[2]);
   if (kind == kSphere) return tsqrt(dot(q, q)) - v[3];
   if (kind == kBox) {
@@ -218,7 +242,12 @@ __device__ __forceinline__ T shape_sdf(const SMCRT_K Prim<T>* P, int i, V3<T> p)
   const T q1 = tsqrt(dot(rad, rad)) - v[8];
   const T q2 = tabs(x - v[7]) - v[7];
   const T o1 = tmax(q1, T(0)), o2 = tmax(q2, T(0));
-  return tmin(tmax(q1, q2), T(0)) + tsqrt(o1 * o1 + o2 * o2);
+  return tmin(tmax(q1, q2), T(0)) + tsqrt(sum_sq(o1, o2));
+}
+template <typename T>
+__device__ __forceinline__ T shape_sdf(const SMCRT_K Prim<T>* P, int i, V3<T> p) {
+  const SMCRT_K T* v = P[i].v;
+  return shape_of<T>(P[i].kind, v, p);
 }
 
 // sin and cos of a twist or displacement angle (moderate arguments):
@@ -535,6 +564,77 @@ __device__ __forceinline__ T region_dist(JobRef a, int r, V3<T> p, LdsCaps lds =
   return region_sdf<T, XF>(a, kptr(a.sc)->reg[r], p);
 }
 
+// An evaluation record in scalar registers.
+typedef uint32_t U16 __attribute__((ext_vector_type(16)));
+template <typename T>
+struct StepV;
+template <>
+struct StepV<float> {
+  U16 w;
+  __device__ __forceinline__ int bits() const { return (int)w[0]; }
+  __device__ __forceinline__ int index() const { return (int)w[1]; }
+  __device__ __forceinline__ float operator[](int k) const { return __builtin_bit_cast(float, (uint32_t)w[2 + k]); }
+  __device__ __forceinline__ float k() const { return (*this)[10]; }
+  __device__ __forceinline__ float inv_k() const { return (*this)[11]; }
+};
+template <>
+struct StepV<double> {
+  U16 w, x;
+  __device__ __forceinline__ int bits() const { return (int)w[0]; }
+  __device__ __forceinline__ int index() const { return (int)w[1]; }
+  __device__ __forceinline__ uint32_t word(int i) const { return i < 16 ? w[i & 15] : x[i & 15]; }
+  __device__ __forceinline__ double operator[](int k) const {
+    return __builtin_bit_cast(double, (uint64_t)word(2 + 2 * k) | ((uint64_t)word(3 + 2 * k) << 32));
+  }
+  __device__ __forceinline__ double k() const { return (*this)[10]; }
+  __device__ __forceinline__ double inv_k() const { return (*this)[11]; }
+};
+__device__ __forceinline__ StepV<float> load_step(const SMCRT_K StepRec<float>* r) {
+  return {*reinterpret_cast<const SMCRT_K U16*>(r)};
+}
+__device__ __forceinline__ StepV<double> load_step(const SMCRT_K StepRec<double>* r) {
+  const SMCRT_K U16* q = reinterpret_cast<const SMCRT_K U16*>(r);
+  return {q[0], q[1]};
+}
+
+// Distance of p to the nearest surface: the smallest |region_dist| over the
+// regions, by the scene's evaluation records.  A lone wave waits for every
+// scalar load it needs; walked through the region, then its primitive's kind,
+// then its parameters, that is four or five waits in a row per region.  A
+// record holds all of it in whole cache lines, and the next one is on its way
+// while this one is worked on.  (With the packets' region rows in LDS: 1e5
+// packets of the 50^3 sphere 7.6 to 7.0 ms.)
+template <typename T, bool XF>
+__device__ __forceinline__ T walk_distance(JobRef a, const SMCRT_K StepRec<T>* rec, int n_steps, V3<T> p,
+                                           LdsCaps lds) {
+  StepV<T> cur = load_step(rec);
+  T dmin = tinf<T>(), d = T(0);
+  for (int i = 1;; ++i) {
+    const bool more = i < n_steps;
+    const StepV<T> next = load_step(rec + (more ? i : 0));
+    const int bits = cur.bits(), kind = bits & kStepKind, op = bits >> kStepOp;
+    if (kind == kStepAccel) {
+      d = accel_sdf<T, XF>(a, p, lds);
+    } else {
+      T b;
+      if (XF && (bits & kStepPlaced)) b = placed_prim_sdf<T>(Tab<T>::prims(a), cur.index(), p);
+      else b = shape_of<T>(kind, cur, p);
+      if (bits & kStepFirst) {
+        d = b;
+      } else if (op == kSmoothUnion) {
+        const T h = tclamp(T(0.5) + T(0.5) * (b - d) * cur.inv_k(), T(0), T(1));
+        d = h * d + (T(1) - h) * b - cur.k() * h * (T(1) - h);
+      } else {
+        const T nb = op == kSubtract ? -b : b;
+        d = op == kUnion ? tmin(d, nb) : tmax(d, nb);
+      }
+    }
+    if (bits & kStepLast) dmin = tmin(dmin, tabs(d));
+    if (!more) return dmin;
+    cur = next;
+  }
+}
+
 // owner of a point: the highest-index region with a negative SDF, else the
 // ambient slot n_regions
 template <typename T, bool XF>
@@ -553,10 +653,16 @@ __device__ __forceinline__ int region_of(JobRef a, V3<T> p) {
 
 // Outside the simulation volume (Sec. 2.3: escape when the volume's box
 // SDF is positive).  The box SDF is positive exactly when the largest of
-// |q_i| - h_i is, so the sign needs no square root; face = 2*axis + side of
-// that largest component, the face the packet left through.
+// |q_i| - h_i is, so the sign needs no square root; volume_face: 2*axis +
+// side of that largest component, the face the packet left through.
 template <typename T>
-__device__ __forceinline__ bool outside_volume(ScP sc, V3<T> p, int* face) {
+__device__ __forceinline__ bool outside_volume(ScP sc, V3<T> p) {
+  const V3<T> c = Tab<T>::bb_c(sc), h = Tab<T>::bb_h(sc);
+  const V3<T> q = p - c;
+  return tmax(tabs(q.x) - h.x, tmax(tabs(q.y) - h.y, tabs(q.z) - h.z)) > T(0);
+}
+template <typename T>
+__device__ __forceinline__ int volume_face(ScP sc, V3<T> p) {
   const V3<T> c = Tab<T>::bb_c(sc), h = Tab<T>::bb_h(sc);
   const V3<T> q = p - c;
   const T ex = tabs(q.x) - h.x, ey = tabs(q.y) - h.y, ez = tabs(q.z) - h.z;
@@ -565,8 +671,7 @@ __device__ __forceinline__ bool outside_volume(ScP sc, V3<T> p, int* face) {
   if (ey > best) { best = ey; ax = 1; }
   if (ez > best) { best = ez; ax = 2; }
   const T qa = ax == 0 ? q.x : (ax == 1 ? q.y : q.z);
-  *face = 2 * ax + (qa > T(0) ? 1 : 0);
-  return best > T(0);
+  return 2 * ax + (qa > T(0) ? 1 : 0);
 }
 
 // Ambient skip: outside every region, the straight path from p along u
@@ -577,6 +682,10 @@ __device__ __forceinline__ bool outside_volume(ScP sc, V3<T> p, int* face) {
 // lies between its planes.)
 template <typename T>
 __device__ __forceinline__ T ambient_free(ScP sc, int nr, V3<T> p, V3<T> u, T delta) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  // keep the divisions here: few steps come this way
+  asm volatile("" : "+v"(u.x), "+v"(u.y), "+v"(u.z));
+#endif
   const V3<T> c = Tab<T>::bb_c(sc), h = Tab<T>::bb_h(sc);
   const T pv[3] = {p.x, p.y, p.z}, uv[3] = {u.x, u.y, u.z};
   const T cv[3] = {c.x, c.y, c.z}, hv[3] = {h.x, h.y, h.z};
@@ -794,17 +903,6 @@ __device__ __forceinline__ T volume_exit(ScP sc, V3<T> p, V3<T> u) {
   return t;
 }
 
-// unit outward normal of region R at p by central differences of step h
-template <bool XF>
-__device__ __forceinline__ V3<double> region_normal(JobRef a, int r, V3<double> p, double h) {
-  V3<double> n;
-  n.x = region_dist<double, XF>(a, r, mk(p.x + h, p.y, p.z)) - region_dist<double, XF>(a, r, mk(p.x - h, p.y, p.z));
-  n.y = region_dist<double, XF>(a, r, mk(p.x, p.y + h, p.z)) - region_dist<double, XF>(a, r, mk(p.x, p.y - h, p.z));
-  n.z = region_dist<double, XF>(a, r, mk(p.x, p.y, p.z + h)) - region_dist<double, XF>(a, r, mk(p.x, p.y, p.z - h));
-  const double inv = 1.0 / __builtin_sqrt(dot(n, n));
-  return inv * n;
-}
-
 // ------------------------------------------------------------------ tallies
 
 struct LdsTallies {
@@ -834,6 +932,15 @@ struct WaveStage {
   double val[kStage];
   int v[kStage];
   int n;
+};
+
+// An interface step of one packet, shared by the lanes of its group (LDS).
+// In: position, direction, region; out: surface point in p, normal there in
+// u, its cosine with the direction, the ray's way to it, the region across.
+constexpr int kSurfaceSlots = 8;  // interface steps a wave takes at a time
+struct SurfaceSlot {
+  double p[3], u[3], c, t_ray;
+  int region, pad;
 };
 
 struct Lane {
@@ -960,7 +1067,7 @@ __device__ __forceinline__ DdaAxis<T> start_axis(T g, T gu, T r, int n, T t0) {
 // stride, so a crossing costs a few compares and selects.
 template <typename T>
 __device__ __forceinline__ void tally_move(JobRef a, V3<T> p, V3<T> u, T len, double w, Lane& ln) {
-  ScP sc = kptr(a.sc);
+  ScP sc = fresh(kptr(a.sc));
   if (a.fluence == nullptr || !(len > T(0))) return;
   const int nx = sc->g_dims[0], ny = sc->g_dims[1], nz = sc->g_dims[2];
   const V3<T> inv = Tab<T>::g_inv(sc);
@@ -1017,7 +1124,10 @@ __device__ __forceinline__ double fresnel(double n1, double n2, double ci, doubl
 
 // ------------------------------------------------------------------ packet
 
-enum State : int { kTransport = 0, kSurface = 1, kInteract = 2 };
+// state of a lane's packet; kDead: the lane has none.  (Held in one vector
+// register: as a flag of its own, "has a packet" would be an execution mask
+// that every join of the control flow has to patch.)
+enum State : int { kTransport = 0, kSurface = 1, kInteract = 2, kDead = 3 };
 
 template <typename T>
 struct Packet {
@@ -1098,11 +1208,36 @@ __device__ __forceinline__ void load_saved(JobRef a, unsigned int i, Packet<T>& 
   vx[2] = s->vx[2];
 }
 
+// What the walk needs of a packet's own region, in LDS.  Lanes are in
+// different regions: read from the scene tables this would be a vector load,
+// which waits for every atomic that the wave has issued before it.
 template <typename T>
-__device__ __forceinline__ void set_region(ScP sc, Packet<T>& pk, int r) {
+struct RegionRow {
+  double mua, mut, n;
+  T mut_t, inv_mut_t;
+  T hg_b, hg_c, hg_d;
+  int iso;
+};
+template <typename T>
+using Regions = const __attribute__((address_space(3))) RegionRow<T>*;
+
+// Fills the table of job a's scene (the ambient slot included) with threads
+// t, t + stride, ...
+template <typename T>
+__device__ __forceinline__ void fill_regions(JobRef a, RegionRow<T>* rows, int t, int stride) {
+  ScP sc = kptr(a.sc);
+  for (int r = t; r <= sc->n_regions; r += stride) {
+    RegRef R = sc->reg[r];
+    rows[r] = RegionRow<T>{R.mua, R.mut, R.n, Tab<T>::mut(R), Tab<T>::inv_mut(R), Tab<T>::hg_b(R), Tab<T>::hg_c(R),
+                           Tab<T>::hg_d(R), R.iso};
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ void set_region(Regions<T> rg, Packet<T>& pk, int r) {
   pk.region = r;
-  pk.mut = Tab<T>::mut(sc->reg[r]);
-  pk.inv_mut = Tab<T>::inv_mut(sc->reg[r]);
+  pk.mut = rg[r].mut_t;
+  pk.inv_mut = rg[r].inv_mut_t;
 }
 
 template <typename T, bool TRACE>
@@ -1246,7 +1381,7 @@ __device__ __forceinline__ void add_absorbed(LdsTallies& L, Lane& ln, int r, dou
 
 // emission, event 0 (Sec. 3.1 sources; Eq. 1)
 template <typename T, bool TRACE, bool XF>
-__device__ void emit(JobRef a, Packet<T>& pk, Lane& ln, LdsTallies& L) {
+__device__ void emit(JobRef a, Regions<T> rg, Packet<T>& pk, Lane& ln, LdsTallies& L) {
   ScP sc = kptr(a.sc);
   const U4 r = philox10(0u, (uint32_t)pk.pid, (uint32_t)(pk.pid >> 32), 0u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
   const T x0 = xi_of<T>(r.w0), x1 = xi_of<T>(r.w1), x3 = xi_of<T>(r.w3);
@@ -1286,7 +1421,7 @@ __device__ void emit(JobRef a, Packet<T>& pk, Lane& ln, LdsTallies& L) {
   pk.links = 0;
   pk.pend = T(0);
   pk.state = kTransport;
-  set_region(sc, pk, region_of<T, XF>(a, pk.p));
+  set_region(rg, pk, region_of<T, XF>(a, pk.p));
   atomicAdd(&L.cnt[kCLaunched], 1ull);
   record<T, TRACE>(a, pk, ln, SMCRT_EV_EMIT);
 }
@@ -1294,9 +1429,9 @@ __device__ void emit(JobRef a, Packet<T>& pk, Lane& ln, LdsTallies& L) {
 // absorption, Henyey-Greenstein scattering, roulette, next free path.
 // Returns false when the packet ends.
 template <typename T, bool TRACE>
-__device__ bool interact(JobRef a, Packet<T>& pk, Lane& ln, LdsTallies& L) {
-  ScP sc = kptr(a.sc);
-  RegRef R = sc->reg[pk.region];
+__device__ bool interact(JobRef a, Regions<T> rg, Packet<T>& pk, Lane& ln, LdsTallies& L) {
+  ScP sc = fresh(kptr(a.sc));
+  const __attribute__((address_space(3))) RegionRow<T>& R = rg[pk.region];
   pk.k += 1;
   ++ln.n_inter;
   const U4 r = philox10(pk.k, (uint32_t)pk.pid, (uint32_t)(pk.pid >> 32), 0u, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
@@ -1318,14 +1453,10 @@ __device__ bool interact(JobRef a, Packet<T>& pk, Lane& ln, LdsTallies& L) {
   T omc;
   if (R.iso) {
     omc = T(2) * (T(1) - x0);
-  } else if constexpr (sizeof(T) == 4) {
-    const float D = R.hg_cf + R.hg_df * x0;
-    const float f = tdiv(R.hg_bf, D);
-    omc = tdiv(R.hg_cf * (1.0f - x0) * (f + R.hg_cf), D);
   } else {
-    const double D = R.hg_c + R.hg_d * x0;
-    const double f = R.hg_b / D;
-    omc = R.hg_c * (1.0 - x0) * (f + R.hg_c) / D;
+    const T D = R.hg_c + R.hg_d * x0;
+    const T f = tdiv(R.hg_b, D);
+    omc = tdiv(R.hg_c * (T(1) - x0) * (f + R.hg_c), D);
   }
   omc = tclamp(omc, T(0), T(2));
   const T ct = T(1) - omc;
