@@ -1296,7 +1296,7 @@ static smcrt_status launch_jobs(smcrt_engine* e, const std::vector<JobSpec>& job
       const size_t cb = align256(sizeof(uint32_t) * ((size_t)h->acc.n_cells + 1));
       a.acc_offsets = reinterpret_cast<const uint32_t*>(base + acc_off[u] + 2 * cb);
       a.acc_ids = reinterpret_cast<const uint32_t*>(base + acc_off[u] + 3 * cb);
-      a.acc_rings = reinterpret_cast<const uint32_t*>(base + acc_off[u]);
+      a.acc_rings = reinterpret_cast<const uint32_t*>(base + acc_off[u] + cb);
     }
     if (tr) {
       a.trace_ids = tr->ids;
@@ -1532,7 +1532,7 @@ extern "C" smcrt_status smcrt_run_ex_static(smcrt_engine* e, const smcrt_scene* 
   if (h->acc.region >= 0) {
     a.acc_offsets = reinterpret_cast<const uint32_t*>(base + acc_off + 2 * cb);
     a.acc_ids = reinterpret_cast<const uint32_t*>(base + acc_off + 3 * cb);
-    a.acc_rings = reinterpret_cast<const uint32_t*>(base + acc_off);
+    a.acc_rings = reinterpret_cast<const uint32_t*>(base + acc_off + cb);
   }
   WalkArgs* d_job = reinterpret_cast<WalkArgs*>(base + jobs_off);
   HIP_TRY(hipMemcpyAsync(base, s->blob.data(), s->blob.size(), hipMemcpyHostToDevice, q), "hipMemcpyAsync(tables)");
@@ -2056,7 +2056,7 @@ static void resident_job(smcrt_server* sv, int s, WalkArgs& a) {
   if (h->acc.region >= 0) {
     a.acc_offsets = reinterpret_cast<const uint32_t*>(sl.dev + sl.acc_off + 2 * sl.acc_cb);
     a.acc_ids = reinterpret_cast<const uint32_t*>(sl.dev + sl.acc_off + 3 * sl.acc_cb);
-    a.acc_rings = reinterpret_cast<const uint32_t*>(sl.dev + sl.acc_off);
+    a.acc_rings = reinterpret_cast<const uint32_t*>(sl.dev + sl.acc_off + sl.acc_cb);
     if (h->acc.caps) {
       a.acc_capd = reinterpret_cast<const double*>(sl.dev + h->acc.cap_offset_d);
       a.acc_capf = reinterpret_cast<const float*>(sl.dev + h->acc.cap_offset_f);

@@ -25,7 +25,8 @@ hipError_t launch_zero_u64(unsigned long long* p, hipStream_t stream);
 // out[i] = in[i] * scale for i < n
 hipError_t launch_scale(const double* in, double* out, size_t n, double scale, hipStream_t stream);
 // device build of the uniform grid of the accelerated region (counts and
-// cursors: n_cells each; offsets: n_cells + 1; ids: the capacity in the header)
+// cursors: n_cells each; offsets: n_cells + 1; ids: the capacity in the header);
+// the ring distances end in cursors
 hipError_t launch_accel_build(const SceneHeader* d_sc, const PrimD* d_pd, int n_prims, int n_cells, uint32_t* counts,
                               uint32_t* cursors, uint32_t* offsets, uint32_t* ids, hipStream_t stream);
 // resident workgroups per CU of the walk kernel of this launch class at this block size

@@ -76,3 +76,33 @@ def test_gathered_interface_steps_leave_the_walk_unchanged(S, eng, W, surface_mi
         assert a[k] == b[k], k
     assert np.max(np.abs(a["fluence_raw"] - b["fluence_raw"])) <= 1e-12 * a["fluence_raw"].max()
     e.close()
+
+
+@pytest.mark.parametrize("cells", [(1, 1, 1), (1, 2, 3), (16, 16, 8), (127, 17, 1), (2048 // 64, 64, 1), (33, 35, 37),
+                                   (256, 256, 3)])
+@pytest.mark.parametrize("n_caps", [1, 3, 300])
+def test_grid_builds_at_the_edges_of_the_scan_tiles(S, eng, W, cells, n_caps):
+    """the accelerated distance is the brute-force one below the margin and a
+    lower bound of it, not below the margin, elsewhere (reading of the grid);
+    tolerance: FP64 rounding of coordinates of size 0.2 (1e-15) and the
+    bound's own relative 2^-20"""
+    desc = W.vessel_scene(3, n_caps=n_caps, n_grid=8)
+    desc["accel_cells"] = list(cells)
+    if n_caps == 1:  # a union of one capsule and a small box: no capsule records
+        desc["prims"].append({"kind": "box", "c": [0.05, 0.05, 0.05], "half": [0.004] * 3})
+        desc["regions"][1]["prims"] = [1, 2]
+    prims = [desc["prims"][i] for i in desc["regions"][1]["prims"]]
+    lo = np.min([np.minimum(p["a"], p["b"]) - p["r"] if "r" in p else np.subtract(p["c"], p["half"]) for p in prims], axis=0)
+    hi = np.max([np.maximum(p["a"], p["b"]) + p["r"] if "r" in p else np.add(p["c"], p["half"]) for p in prims], axis=0)
+    margin = np.max((hi - lo) / np.array(cells))
+    pts = np.random.default_rng(1).uniform(-0.02, 0.22, (4000, 3))
+    d, own = S.distance(desc, pts, engine=eng)
+    a, own_a = S.distance(desc, pts, engine=eng, accelerated=True)
+    d, a = d[:, 1], a[:, 1]
+    near = d < margin
+    assert np.all(np.abs(a[near] - d[near]) <= 1e-14)
+    assert np.all(a <= d + 1e-14)
+    inside = np.all((pts > lo - margin) & (pts < hi + margin), axis=1)
+    far = ~near & inside
+    assert np.all(a[far] >= margin * (1 - 1e-12))
+    assert np.array_equal(own, own_a)
