@@ -796,14 +796,34 @@ static smcrt_status pack_accel(const smcrt_scene* s, SceneHeader* h, const std::
   return SMCRT_OK;
 }
 
+static void accel_floats(const Accel& A, AccelRec<double>& o) {
+  std::memcpy(o.lo, A.lo, sizeof(o.lo));
+  std::memcpy(o.inv_cell, A.inv_cell, sizeof(o.inv_cell));
+  o.margin = A.margin;
+  o.cell_min = A.cell_min;
+}
+static void accel_floats(const Accel& A, AccelRec<float>& o) {
+  std::memcpy(o.lo, A.lof, sizeof(o.lo));
+  std::memcpy(o.inv_cell, A.inv_cellf, sizeof(o.inv_cell));
+  o.margin = A.marginf;
+  o.cell_min = A.cell_minf;
+}
+
 template <typename T>
 static void pack_steps(const smcrt_scene* s, const SceneHeader* h, const Prim<T>* prims, StepRec<T>* out) {
   for (int r = 0; r < h->n_regions; ++r) {
     const Region& R = h->reg[r];
     if (r == s->accel_region) {
-      out->bits = kStepAccel | kStepFirst | kStepLast;
-      out->index = R.first;
-      ++out;
+      const Accel& A = h->acc;
+      AccelRec<T> o = {};
+      o.bits = kStepAccel | kStepFirst | kStepLast | (A.caps ? kStepCaps : 0);
+      o.index = A.first_prim;
+      accel_floats(A, o);
+      std::memcpy(o.dims, A.dims, sizeof(o.dims));
+      o.n_prims = A.n_prims;
+      o.capacity[0] = (uint32_t)A.capacity;
+      o.capacity[1] = (uint32_t)(A.capacity >> 32);
+      std::memcpy(out++, &o, sizeof(o));
       continue;
     }
     for (int i = 0; i < R.count; ++i, ++out) {
@@ -873,11 +893,6 @@ static smcrt_status pack(smcrt_scene* s) {
     h->reg[r].seg = s->segment ? seg_rule(s, hr) : kSegNone;
     first += (int)hr.prims.size();
   }
-  pack_steps(s, h, pd, reinterpret_cast<StepRec<double>*>(s->blob.data() + step_d));
-  pack_steps(s, h, pf, reinterpret_cast<StepRec<float>*>(s->blob.data() + step_f));
-  h->n_steps = (int32_t)n_steps;
-  h->step_offset_d = step_d;
-  h->step_offset_f = step_f;
   fill_region(h->reg[s->regions.size()], 0.0, 0.0, 0.0, s->n_ambient, 0.0, kUnion, 0, 0);
   h->delta = s->delta;
   h->deltaf = (float)s->delta;
@@ -987,6 +1002,11 @@ static smcrt_status pack(smcrt_scene* s) {
     h->acc.cap_offset_d = cap_d;
     h->acc.cap_offset_f = cap_f;
   }
+  pack_steps(s, h, pd, reinterpret_cast<StepRec<double>*>(s->blob.data() + step_d));
+  pack_steps(s, h, pf, reinterpret_cast<StepRec<float>*>(s->blob.data() + step_f));
+  h->n_steps = (int32_t)n_steps;
+  h->step_offset_d = step_d;
+  h->step_offset_f = step_f;
   h->prim_offset_d = off_d;
   h->prim_offset_f = off_f;
   h->blob_bytes = bytes;
@@ -1074,10 +1094,11 @@ static bool brick_tally(const smcrt_opts& o, const SceneHeader* h) {
 // kLaunchXf for placed or modified primitives; FP32 SDF jobs whose
 // accelerated region is plain capsules that fit the LDS table run in the
 // staged-capsule kernel (not for traces, which run one packet per thread);
-// scenes with segment-traced steps (plain SDF scenes: the packer checks) in
-// the segment kernel.
+// scenes with segment-traced steps (plain SDF scenes: the packer checks) and
+// plain scenes with over-relaxed ones in the segment kernel: what those steps
+// remember from one to the next would cost every other walk two registers.
 static int job_class(const smcrt_opts& o, const SceneHeader* h, bool trace) {
-  if (h->segment) return kLaunchSegment;
+  if (h->geometry == kGeomSdf && !h->xf && (h->segment || h->relax > 1.0)) return kLaunchSegment;
   const int c = h->geometry + (h->xf ? kLaunchXf : 0);
   if (!trace && !o.no_stage && c == kGeomSdf && o.precision == SMCRT_PREC_F32 && h->acc.region >= 0 && h->acc.caps &&
       h->acc.n_prims <= kStageCaps)

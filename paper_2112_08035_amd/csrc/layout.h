@@ -29,7 +29,7 @@ enum Geometry : int32_t { kGeomSdf = 0, kGeomVoxel = 1 };
 // has placed or modified primitives (a separate kernel instantiation);
 // kLaunchStaged: an FP32 SDF job whose accelerated region is plain capsules
 // that fit the workgroup's LDS table (the staged-capsule kernel);
-// kLaunchSegment: an SDF job with segment-traced steps
+// kLaunchSegment: an SDF job with segment-traced or over-relaxed steps
 enum LaunchClass : int32_t { kLaunchXf = 2, kLaunchStaged = 4, kLaunchSegment = 5, kLaunchClasses = 6 };
 // segment-tracing rule of a region: how the tangent bounds of its members
 // bound the way to its surface (none: the distance alone)
@@ -90,6 +90,7 @@ enum StepBits : int32_t {
   kStepFirst = 16,    // first record of its region
   kStepLast = 32,     // last record of its region
   kStepPlaced = 64,   // placed or modified: evaluated from its Prim record
+  kStepCaps = 128,    // kStepAccel: Accel::caps
   kStepOp = 8         // shift of the region's RegionOp
 };
 template <typename T>
@@ -100,7 +101,17 @@ struct StepRec {
   T k, inv_k;     // smooth-union radius
   int32_t pad[sizeof(T) == 4 ? 2 : 6];
 };
+// The record of the accelerated region holds what a query of its grid needs.
+template <typename T>
+struct AccelRec {
+  int32_t bits;
+  int32_t index;  // its first primitive
+  T lo[3], inv_cell[3], margin, cell_min;
+  int32_t dims[3], n_prims;
+  uint32_t capacity[2];  // low and high word
+};
 static_assert(sizeof(StepRec<float>) == 64 && sizeof(StepRec<double>) == 128, "whole cache lines");
+static_assert(sizeof(AccelRec<float>) == 64 && sizeof(AccelRec<double>) <= 128, "a record");
 
 struct Region {
   int32_t first, count, op;       // primitive range (region order) and CSG op

@@ -61,8 +61,8 @@ __device__ __forceinline__ void wave_fence() {
 }
 
 // region_dist<double> of a region that differs between lanes.  Scenes with
-// placed primitives take the regions one after the other, so that their
-// many parameters stay scalar loads.
+// placed primitives take the regions one after the other, so that their many
+// parameters stay scalar loads.
 template <bool XF>
 __device__ __forceinline__ double lane_region_dist(JobRef a, int r, V3<double> p) {
   if constexpr (XF) {
@@ -90,7 +90,7 @@ template <bool XF>
 __device__ __forceinline__ void surface_geometry(JobRef a, SurfaceSlot* S, int n, int lane) {
   ScP sc = fresh(kptr(a.sc));
   const int group = lane >> 3, sub = lane & 7;
-  const bool on = group < n;
+  const bool on = group < n, first = on && sub == 0;
   SurfaceSlot& s = S[on ? group : 0];
   const int nr = sc->n_regions;
   double dj = 0.0;
@@ -152,7 +152,7 @@ __device__ __forceinline__ void surface_geometry(JobRef a, SurfaceSlot* S, int n
         }
       }
       wave_fence();
-      if (on && sub == 0) {
+      if (first) {
         if (step == rounds) {
           s.p[0] = ps.x; s.p[1] = ps.y; s.p[2] = ps.z;
           s.t_ray = t_ray;
@@ -164,7 +164,7 @@ __device__ __forceinline__ void surface_geometry(JobRef a, SurfaceSlot* S, int n
       wave_fence();
     }
   }
-  if (on && sub == 0 && s.c != 0.0) s.region = r2;
+  if (first && s.c != 0.0) s.region = r2;
   wave_fence();
 }
 
@@ -253,6 +253,8 @@ __device__ __forceinline__ void surface_event(JobRef a, Regions<T> rg, const Sur
   }
 }
 
+constexpr int kDueMin = 32;  // see the sphere-tracing steps
+
 // The persistent walk over a table of jobs (scene tables, seed, packet
 // range, outputs).  Each wave works on one job at a time, so the job's
 // tables are wave uniform and come through the scalar cache; waves start
@@ -278,7 +280,8 @@ __device__ __forceinline__ void surface_event(JobRef a, Regions<T> rg, const Sur
 // ids.  A separate instantiation: the save and resume paths cost registers
 // the plain walk does not spend.
 //
-// SEG (kLaunchSegment jobs): every evaluation also bounds the way along the
+// SEG (kLaunchSegment jobs): over-relaxed steps (in the XF kernels too) or, for
+// segment-tracing scenes: every evaluation also bounds the way along the
 // ray to each region's surface (segment tracing), and a step runs to the
 // nearest such bound less delta when that is longer than the distance.
 template <typename T, bool TRACE, int GEOM, bool XF, bool STAGE, bool EPOCH, bool SEG>
@@ -288,6 +291,7 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
   static_assert(!EPOCH || !TRACE, "epochs are for runs, not traces");
   static_assert(!SEG || (GEOM == kGeomSdf && !XF && !STAGE), "segment tracing: plain SDF walks");
   constexpr int kWaves = STAGE ? 16 : 4;
+  constexpr bool kRelax = SEG || XF;  // kernels whose scenes may take over-relaxed steps
   const SMCRT_K WalkArgs* jobs = kptr(job_table);
   __shared__ LdsTallies Lw[kWaves];
   __shared__ WaveStage Sw[kWaves];
@@ -330,6 +334,7 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
   ln.n_steps = ln.n_inter = ln.n_pieces = ln.n_atomics = 0;
   ln.rec = nullptr;
   ln.n_rec = 0;
+  WaveTally wt = {0, 0ull, 0ull};
 
   // resident serving: a launch with a deadline stops when the device wall
   // clock has run deadline ticks past its start (the workgroup's start in
@@ -488,61 +493,76 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
         }
       }
 
-      // ---- sphere-tracing steps (Sec. 2.3): one, and further ones at once
-      // while every packet of the wave is on its way (or waits at a surface
-      // for company): a wave with few packets left then takes step after
-      // step without passing through the rest of the loop.  The longest
-      // packets graze surfaces for thousands of steps, and a short launch
-      // lasts as long as they do: 1e5 packets of the 50^3 sphere 7.0 to
-      // 5.0 ms, 64 such runs in a batch 45.9 to 41.0 ms
-      if (GEOM == kGeomSdf && __ballot(pk.state == kTransport) != 0ull) {
+      // ---- sphere-tracing steps (Sec. 2.3), one after the other until
+      // kDueMin / 64 of the live lanes are due for the rest of the loop (an
+      // interaction or their end), or company has come together at the
+      // surfaces: the rest of the loop costs as much for one lane as for all.
+      // A wave with few packets left thereby takes step after step without
+      // passing through it; the longest packets graze surfaces for thousands
+      // of steps, and a short launch lasts as long as they do.  64 runs of
+      // 1e5 packets in a batch: the rest of the loop after every step 45.9
+      // ms, as soon as one lane is due 38.2, a quarter 37.6, half 32.0, two
+      // thirds 31.6; 1e5 packets of the 50^3 sphere 7.0, 4.24, -, 3.94, -;
+      // 1e7 of the slab 295.2 (one lane) and 294.2 (half).
+      uint64_t on = GEOM == kGeomSdf ? __ballot(pk.state == kTransport) : 0ull;
+      if (on != 0ull) {
         const ScP hot = fresh(sc);
         const SMCRT_K StepRec<T>* recs = fresh(Tab<T>::steps(a));
+        const int nlive = __popcll(lmask);
         int inner = 0;
-        uint64_t on, at;
+        uint64_t at;
         do {
           const ScP sc = hot;
           if (pk.state == kTransport) {
-            pk.safe = T(-1);
-            if (++pk.steps > max_steps || pk.k > max_events) {
-              atomicAdd(&L.stalled, pk.w);
-              atomicAdd(&L.cnt[kCStalls], 1ull);
-              record<T, TRACE>(a, pk, ln, SMCRT_EV_STALL);
-              pk.state = kDead;
-            } else {
-              ++ln.n_steps;
-              T dmin = tinf<T>(), tseg = tinf<T>();
-              if constexpr (SEG) {
-                const T err = Tab<T>::seg_err(sc);
-                for (int r = 0; r < nr; ++r) {
-                  T tb;
-                  dmin = tmin(dmin, tabs(region_seg<T, XF>(a, r, pk.p, pk.u, err, &tb)));
-                  tseg = tmin(tseg, tb);
-                }
-              } else {
-                dmin = walk_distance<T, XF>(a, recs, n_steps, pk.p, caps_lds);
+            ++pk.steps;
+            const bool stall = pk.steps > max_steps || pk.k > max_events;
+            T dmin = tinf<T>(), tseg = tinf<T>();
+            if (SEG && sc->segment) {
+              const T err = Tab<T>::seg_err(sc);
+              for (int r = 0; r < nr; ++r) {
+                T tb;
+                dmin = tmin(dmin, tabs(region_seg<T, XF>(a, r, pk.p, pk.u, err, &tb)));
+                tseg = tmin(tseg, tb);
               }
-              const T om = Tab<T>::relax(sc);
-              const bool outside = outside_volume<T>(sc, pk.p);
+            } else {
+              dmin = walk_distance<T, XF>(a, recs, n_steps, pk.p, caps_lds);
+            }
+            const T om = kRelax ? Tab<T>::relax(sc) : T(1);
+            const bool outside = outside_volume<T>(sc, pk.p);
+            const T s = pk.mut > T(0) ? (T)(pk.tau * (double)pk.inv_mut) : tinf<T>();
+            const bool near = s <= dmin;  // the optical depth runs out before any surface
+            // Nearly every step moves dmin on, or s to the interaction.  All
+            // that is not such a step goes through one branch: a lone wave
+            // takes 30 to 50 cycles for each branch on a vector compare, as
+            // long as six dependent instructions
+            bool inter = near, move = true, rel = false, jump = false;
+            T len = near ? s : dmin;
+            if ((SEG && sc->segment) || om > T(1) || stall || outside || (!near && (dmin < delta || pk.region == nr))) {
               bool rejected = false;
-              if (om > T(1) && pk.pl < T(0)) {
+              if (om > T(1) && !stall && pk.pl < T(0)) {
                 // check of an over-relaxed step (Sec. 5): the open balls of
                 // radius pd at its start and dmin at its end hold no surface;
                 // unless they cover the step with a margin of delta it goes back
                 // to the plain step of pd, and this evaluation is spent
-                const T len = -pk.pl;
-                if (pk.pd + dmin >= len + delta) {
-                  pk.pl = len;
+                const T over = -pk.pl;
+                if (pk.pd + dmin >= over + delta) {
+                  pk.pl = over;
                 } else {
                   rejected = true;
-                  step_along(pk, pk.pd - len);
+                  step_along(pk, pk.pd - over);
                   pk.pl = pk.pd;
                 }
               }
-              const T s = pk.mut > T(0) ? (T)(pk.tau * (double)pk.inv_mut) : tinf<T>();
-              const bool near = s <= dmin;  // the optical depth runs out before any surface
-              if (rejected) {
+              if (stall) {
+                atomicAdd(&L.stalled, pk.w);
+                atomicAdd(&L.cnt[kCStalls], 1ull);
+                record<T, TRACE>(a, pk, ln, SMCRT_EV_STALL);
+                pk.state = kDead;
+                --ln.n_steps;
+                move = false;
+              } else if (rejected) {
                 // the next evaluation starts from the plain step's end
+                move = false;
               } else if (outside) {  // outside the simulation volume
                 const int face = volume_face<T>(sc, pk.p);
                 atomicAdd(&L.escaped[face], pk.w);
@@ -550,23 +570,24 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
                 detect<T>(a, pk, face, Tab<T>::bb_c(sc, face >> 1) + ((face & 1) ? Tab<T>::bb_h(sc, face >> 1) : -Tab<T>::bb_h(sc, face >> 1)));
                 record<T, TRACE>(a, pk, ln, SMCRT_EV_ESCAPE);
                 pk.state = kDead;
+                move = false;
               } else if (!near && dmin < delta) {
                 pk.state = kSurface;
+                move = false;
               } else {
                 // segment tracing: a step may run to the nearest bound along the
                 // ray less delta, or delta past the volume's boundary when that
                 // comes first
                 T seg = dmin;
-                if constexpr (SEG) {
+                if (SEG && sc->segment) {
                   if (!near && tseg - delta > dmin) seg = tmax(dmin, tmin(tseg - delta, volume_exit<T>(sc, pk.p, pk.u) + delta));
                 }
                 // the packet interacts where its optical depth runs out: within
                 // the ball of radius dmin about the step's start, which holds no
                 // surface, or (segment tracing) on the free segment ahead, where
                 // plain steps would reach it and no free ball about it is known
-                const bool inter = near || (SEG && seg > dmin && s <= seg);
-                T len = inter ? s : dmin;
-                bool rel = false, skip = false;
+                inter = near || (SEG && seg > dmin && s <= seg);
+                len = inter ? s : dmin;
                 if (om > T(1)) {
                   // an over-relaxed step of omega * dmin when it would pass its
                   // check were the surface a plane met at the angle the previous
@@ -586,30 +607,38 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
                   const T ulp4 = sizeof(T) == 4 ? T(0x1p-21) : T(0x1p-50);
                   if (tf > len && tf >= seg && T(0.5) * delta >= ulp4 * (pmax + tf)) {
                     len = tf;
-                    skip = true;
+                    jump = true;
                   }
                 }
-                const bool segment = SEG && !inter && !skip && seg > len;
-                if (segment) len = seg;
-                advance(pk, len);
-                const double left = pk.tau - (double)pk.mut * (double)len;
-                pk.tau = inter ? 0.0 : left;
-                pk.state = inter ? kInteract : kTransport;
-                if (near && pk.region < nr) {
-                  pk.safe = dmin - s;
-                  pk.links = 0;
+                if (SEG && !inter && !jump && seg > len) {
+                  len = seg;
+                  jump = true;
+                  rel = false;
                 }
-                if (!inter) {
-                  pk.pd = skip || segment ? T(-1) : dmin;
-                  pk.pl = rel && !skip ? -len : len;
-                }
+              }
+            }
+            ++ln.n_steps;
+            pk.safe = near && move && pk.region < nr ? dmin - s : T(-1);
+            if (move) {
+              advance(pk, len);
+              const double left = pk.tau - (double)pk.mut * (double)len;
+              pk.tau = inter ? 0.0 : left;
+              pk.state = inter ? kInteract : kTransport;
+              pk.links = near ? 0 : pk.links;
+              if constexpr (kRelax) {
+                pk.pd = inter ? pk.pd : (jump ? T(-1) : dmin);
+                pk.pl = inter ? pk.pl : (rel && !jump ? -len : len);
               }
             }
           }
           on = __ballot(pk.state == kTransport);
+          if (on == lmask) continue;
           at = __ballot(pk.state == kSurface);
+          if (on == 0ull || __popcll(lmask & ~(on | at)) * 64 >= kDueMin * nlive ||
+              __popcll(at) * 64 >= B.surface_min * nlive)
+            break;
           // (resident serving: back to the deadline every 16 steps)
-        } while ((on | at) == lmask && __popcll(at) * 64 < B.surface_min * __popcll(lmask) && !(EPOCH && ++inner == 16));
+        } while (!EPOCH || ++inner < 16);
       }
 
       // ---- interface steps, gathered: up to eight packets an iteration,
@@ -644,7 +673,9 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
       // on an interface (its position jumps or its direction changes next)
       // credit their straight path since the last event to the grid, together
       if constexpr (GEOM == kGeomSdf) {
-        if (pk.pend > T(0) && (pk.state >= kInteract || hit >= 0)) flush_tally<T>(a, pk, ln);
+        const bool due = pk.pend > T(0) && (pk.state >= kInteract || hit >= 0);
+        tally_path<T>(a, pk, due, ln, wt);
+        if (due) pk.pend = T(0);
         if (hit >= 0) {
           pk.pend = T(0);
           surface_event<T, TRACE>(a, rg, Hw[wib][hit], pk, ln, L);
@@ -663,18 +694,21 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
       // a drain (the region's coefficients in the interaction) waits until
       // every drained atomic has completed at the L2.  Issued here, they
       // complete while the next iteration's step runs.
-      if (a.fluence != nullptr) stage_drain(a.fluence, *ln.stage, kDrain, lane);
+      if (a.fluence != nullptr) {
+        if constexpr (GEOM == kGeomSdf) tally_drain(a.fluence, *ln.stage, wt, kDrain, lane);
+        else stage_drain(a.fluence, *ln.stage, kDrain, lane);
+      }
     }
 
     if constexpr (TRACE) {
       const int id = blockIdx.x * blockDim.x + threadIdx.x;
       if (id < a.n_trace) a.trace_count[id] = ln.n_rec < a.max_records ? ln.n_rec : a.max_records;
-      flush_wave(a, ln, L, lane);
+      flush_wave(a, ln, wt, L, lane);
       break;
     } else if constexpr (STAGE) {
       // job drained by this wave: hand in its sums; once every wave is done
       // with the job (and its table), the workgroup takes the next one
-      flush_wave(a, ln, L, lane);
+      flush_wave(a, ln, wt, L, lane);
       __syncthreads();
       if (wib == 0) {
         const bool late = EPOCH && __builtin_amdgcn_s_memrealtime() - t0 > B.deadline;
@@ -687,11 +721,11 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
       caps_lds = (LdsCaps)caps_fill;
       if (!stage_caps(jobs[cur], caps_fill)) caps_lds = nullptr;
       fill_regions<T>(jobs[cur], rows, threadIdx.x, blockDim.x);
-      __syncthreads();
+        __syncthreads();
     } else {
       // job drained by this wave (or the epoch ended): hand in its sums,
       // take the next job
-      flush_wave(a, ln, L, lane);
+      flush_wave(a, ln, wt, L, lane);
       if (stop) break;
       cur = pick_job(jobs, B, cur + 1);
       if (cur < 0) break;

@@ -37,6 +37,16 @@ __device__ __forceinline__ const SMCRT_K X* fresh(const SMCRT_K X* p) {
   return (const SMCRT_K X*)v;
 }
 
+// Ends an expression: the compiler fuses no multiplication and addition
+// across it, so what is computed on either side rounds the same wherever the
+// code is inlined.
+template <typename T>
+__device__ __forceinline__ void hold(T& x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(x));
+#endif
+}
+
 // ------------------------------------------------------------------ types
 
 template <typename T>
@@ -86,6 +96,16 @@ template <typename T>
 __device__ __forceinline__ T tabs(T a) {
   if constexpr (sizeof(T) == 4) return __builtin_fabsf(a);
   else return __builtin_fabs(a);
+}
+template <typename T>
+__device__ __forceinline__ T tfma(T a, T b, T c) {
+  if constexpr (sizeof(T) == 4) return __builtin_fmaf(a, b, c);
+  else return __builtin_fma(a, b, c);
+}
+// dot() with its roundings fixed: the same wherever it is inlined
+template <typename T>
+__device__ __forceinline__ T fdot(V3<T> a, V3<T> b) {
+  return tfma(a.z, b.z, tfma(a.x, b.x, a.y * b.y));
 }
 template <typename T>
 __device__ __forceinline__ T tclamp(T x, T lo, T hi) { return tmin(tmax(x, lo), hi); }
@@ -218,28 +238,28 @@ __device__ __forceinline__ double sum_sq(double x, double y) { return x * x + y 
 template <typename T, typename Params>
 __device__ __forceinline__ T shape_of(int kind, const Params& v, V3<T> p) {
   const V3<T> q = p - mk(v[0], v[1], v[2]);
-  if (kind == kSphere) return tsqrt(dot(q, q)) - v[3];
+  if (kind == kSphere) return tsqrt(fdot(q, q)) - v[3];
   if (kind == kBox) {
     const T ex = tabs(q.x) - v[3], ey = tabs(q.y) - v[4], ez = tabs(q.z) - v[5];
     const V3<T> o = mk(tmax(ex, T(0)), tmax(ey, T(0)), tmax(ez, T(0)));
-    return tsqrt(dot(o, o)) + tmin(tmax(ex, tmax(ey, ez)), T(0));
+    return tsqrt(fdot(o, o)) + tmin(tmax(ex, tmax(ey, ez)), T(0));
   }
   const V3<T> e = mk(v[3], v[4], v[5]);
   if (kind == kTorus) {  // e unit axis, v[6] = ring radius R, v[7] = tube radius r
-    const T x = dot(q, e);
+    const T x = fdot(q, e);
     const V3<T> rad = q - x * e;
-    const T rho = tsqrt(dot(rad, rad)) - v[6];
-    return tsqrt(rho * rho + x * x) - v[7];
+    const T rho = tsqrt(fdot(rad, rad)) - v[6];
+    return tsqrt(tfma(x, x, rho * rho)) - v[7];
   }
   if (kind == kCapsule) {  // e = b - a, v[6] = 1/|b-a|^2
-    const T t = tclamp(dot(q, e) * v[6], T(0), T(1));
+    const T t = tclamp(fdot(q, e) * v[6], T(0), T(1));
     const V3<T> d = q - t * e;
-    return tsqrt(dot(d, d)) - v[7];
+    return tsqrt(fdot(d, d)) - v[7];
   }
   // capped cylinder: e unit axis, v[6] = L, v[7] = L/2, v[8] = r
-  const T x = dot(q, e);
+  const T x = fdot(q, e);
   const V3<T> rad = q - x * e;
-  const T q1 = tsqrt(dot(rad, rad)) - v[8];
+  const T q1 = tsqrt(fdot(rad, rad)) - v[8];
   const T q2 = tabs(x - v[7]) - v[7];
   const T o1 = tmax(q1, T(0)), o2 = tmax(q2, T(0));
   return tmin(tmax(q1, q2), T(0)) + tsqrt(sum_sq(o1, o2));
@@ -343,9 +363,9 @@ __device__ __forceinline__ T further_shape_sdf(const SMCRT_K Prim<T>* P, int i, 
   if (kind == kCone) {  // (axial x, radial y) half plane: the two caps and the slanted side
     const V3<T> e = mk(v[3], v[4], v[5]);
     const T L = v[6], ra = v[7], rb = v[8];
-    const T x = dot(q, e);
+    const T x = fdot(q, e);
     const V3<T> rad = q - x * e;
-    const T y = tsqrt(dot(rad, rad));
+    const T y = tsqrt(fdot(rad, rad));
     const T d = tmin(tmin(seg2_dist(x, y, T(0), T(0), T(0), ra), seg2_dist(x, y, L, T(0), L, rb)),
                      seg2_dist(x, y, T(0), ra, L, rb));
     const bool inside = x > T(0) && x < L && y < ra + (rb - ra) * x / L;
@@ -367,22 +387,27 @@ __device__ __forceinline__ T further_shape_sdf(const SMCRT_K Prim<T>* P, int i, 
     if (y < h && T(1.7320508075688772935) * x + y < T(2) * h) d2 = -d2;
     const T dz = tabs(q.z) - hz;
     const T o1 = tmax(d2, T(0)), o2 = tmax(dz, T(0));
-    return tmin(tmax(d2, dz), T(0)) + tsqrt(o1 * o1 + o2 * o2);
+    return tmin(tmax(d2, dz), T(0)) + tsqrt(tfma(o2, o2, o1 * o1));
   }
   // ellipsoid: rmin (|q / r| - 1), 1-Lipschitz and zero on the surface
   const V3<T> u = mk(q.x * v[3], q.y * v[4], q.z * v[5]);
-  return v[6] * (tsqrt(dot(u, u)) - T(1));
+  return v[6] * (tsqrt(fdot(u, u)) - T(1));
 }
 
+// SDF of a placed or modified primitive.  Every product that a sum takes up is
+// an explicit fma: inlined into the walk's steps and called from elsewhere,
+// it has to round the same.
 template <typename T>
-__device__ __attribute__((noinline)) T placed_prim_sdf(const SMCRT_K Prim<T>* P, int i, V3<T> p) {
+__device__ __forceinline__ T placed_prim(const SMCRT_K Prim<T>* P, int i, V3<T> p) {
+  hold(p.x);
+  hold(p.y);
+  hold(p.z);
   const SMCRT_K Prim<T>& Q = P[i];
   const int fl = Q.flags;
   V3<T> q = p;
   if (fl & kPlaced) {
     const V3<T> d = p - mk(Q.t[0], Q.t[1], Q.t[2]);
-    q = mk(Q.m[0] * d.x + Q.m[1] * d.y + Q.m[2] * d.z, Q.m[3] * d.x + Q.m[4] * d.y + Q.m[5] * d.z,
-           Q.m[6] * d.x + Q.m[7] * d.y + Q.m[8] * d.z);
+    q = mk(fdot(mk(Q.m[0], Q.m[1], Q.m[2]), d), fdot(mk(Q.m[3], Q.m[4], Q.m[5]), d), fdot(mk(Q.m[6], Q.m[7], Q.m[8]), d));
   }
   // repetition: to the nearest copy; b = distance to the nearest face of its
   // cell with another copy behind it
@@ -394,8 +419,8 @@ __device__ __attribute__((noinline)) T placed_prim_sdf(const SMCRT_K Prim<T>* P,
       const int n = Q.rep_n[a];
       const T c = Q.rep_c[a], half = T(0.5) * T(n - 1) * c;
       // clamp before converting: a far point must not overflow the int
-      const int k = (int)tclamp(floor((c3[a] + half) / c + T(0.5)), T(0), T(n - 1));
-      c3[a] -= T(k) * c - half;
+      const int k = (int)tclamp(floor(tfma(c, T(0.5) * T(n - 1), c3[a]) / c + T(0.5)), T(0), T(n - 1));
+      c3[a] -= tfma(T(k), c, -half);
       if (c3[a] > T(0) && k < n - 1) b = tmin(b, T(0.5) * c - c3[a]);
       if (c3[a] < T(0) && k > 0) b = tmin(b, T(0.5) * c + c3[a]);
     }
@@ -403,13 +428,13 @@ __device__ __attribute__((noinline)) T placed_prim_sdf(const SMCRT_K Prim<T>* P,
   }
   T dcyl = T(0);
   if (fl & kTwisted) {  // distance to the bounding cylinder, then untwist by -k z (unbend: -k x) about z
-    const T q1 = tsqrt(q.x * q.x + q.y * q.y) - Q.twist_rho;
+    const T q1 = tsqrt(tfma(q.x, q.x, q.y * q.y)) - Q.twist_rho;
     const T q2 = tabs(q.z - Q.twist_zc) - Q.twist_zh;
     const T o1 = tmax(q1, T(0)), o2 = tmax(q2, T(0));
-    dcyl = tmin(tmax(q1, q2), T(0)) + tsqrt(o1 * o1 + o2 * o2);
+    dcyl = tmin(tmax(q1, q2), T(0)) + tsqrt(tfma(o1, o1, o2 * o2));
     T sn, cs;
     tsincos(-Q.twist_k * ((fl & kBent) ? q.x : q.z), &sn, &cs);
-    q = mk(cs * q.x - sn * q.y, sn * q.x + cs * q.y, q.z);
+    q = mk(tfma(cs, q.x, -(sn * q.y)), tfma(sn, q.x, cs * q.y), q.z);
   }
   const V3<T> e = mk(q.x - tclamp(q.x, -Q.elong[0], Q.elong[0]), q.y - tclamp(q.y, -Q.elong[1], Q.elong[1]),
                      q.z - tclamp(q.z, -Q.elong[2], Q.elong[2]));
@@ -420,22 +445,39 @@ __device__ __attribute__((noinline)) T placed_prim_sdf(const SMCRT_K Prim<T>* P,
     tsincos(Q.disp_f * q.x, &sx, &cx);
     tsincos(Q.disp_f * q.y, &sy, &cy);
     tsincos(Q.disp_f * q.z, &sz, &cz);
-    d = (d + Q.disp_a * sx * sy * sz) * Q.disp_inv_lip;
+    d = tfma(Q.disp_a * sx * sy, sz, d) * Q.disp_inv_lip;
   }
   if (fl & kTwisted) d = dcyl > T(0) ? dcyl : d * Q.inv_lip;
   if (fl & kRepeated) d = tmin(d, Q.rep_gap + b);
   if (fl & kPlaced) d *= Q.s;
+  hold(d);
   return d;
+}
+// The same as a function, for the rarer places.  UNI: i is the same for every
+// lane.  A function's arguments arrive in vector registers; taken back to
+// scalar ones, the parameters are scalar loads instead of vector loads that
+// wait for the wave's atomics (2e5 packets of the gallery scene 67.6 to 52
+// ms, and to 49 ms with the steps' evaluations inlined; inlined everywhere
+// 50.5 ms).
+template <typename T, bool UNI>
+__device__ __attribute__((noinline)) T placed_prim_sdf(const SMCRT_K Prim<T>* P, int i, V3<T> p) {
+  if constexpr (UNI) {
+    const uint64_t v = (uint64_t)P;
+    P = (const SMCRT_K Prim<T>*)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
+                                 (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v));
+    i = __builtin_amdgcn_readfirstlane(i);
+  }
+  return placed_prim<T>(P, i, p);
 }
 
 // XF: the scene has placed or modified primitives.  Scenes without them
 // run kernels that never call placed_prim_sdf: a call in the sphere-tracing
 // loop makes the caller keep its live values out of the registers the
 // callee may use, which pushed the FP32 walk over its register budget.
-template <typename T, bool XF>
+template <typename T, bool XF, bool UNI = true>
 __device__ __forceinline__ T prim_sdf(const SMCRT_K Prim<T>* P, int i, V3<T> p) {
   if constexpr (XF) {
-    if (P[i].flags != 0) return placed_prim_sdf<T>(P, i, p);
+    if (P[i].flags != 0) return placed_prim_sdf<T, UNI>(P, i, p);
   }
   return shape_sdf(P, i, p);
 }
@@ -474,96 +516,6 @@ __device__ __forceinline__ T cap_sdf(T a0, T a1, T a2, T e0, T e1, T e2, T inv, 
   return tsqrt(dot(d, d)) - r;
 }
 
-// Lower bound of the accelerated region's SDF at p in a cell that lists no
-// primitive, from the cell's ring distance k (in cells) to the nearest cell
-// that lists one: every surface point lies in such a cell, so the surface is
-// at least k - 1 whole cells plus p's way to its own cell's faces away (the
-// smallest side counted; cell coordinates cx, cy, cz of p and its cell
-// ix, iy, iz).  Never below the margin; a relative 2^-20 less against
-// rounding.
-template <typename T>
-__device__ __forceinline__ T ring_bound(JobRef a, const SMCRT_K Accel& A, int c, T cx, T cy, T cz, int ix, int iy,
-                                        int iz) {
-  const T m = Tab<T>::acc_margin(A);
-  if (a.acc_rings == nullptr) return m;
-  const uint32_t k = kptr(a.acc_rings)[c];
-  const T fx = cx - T(ix), fy = cy - T(iy), fz = cz - T(iz);
-  const T f = tmin(tmin(tmin(fx, T(1) - fx), tmin(fy, T(1) - fy)), tmin(fz, T(1) - fz));
-  const T r = (T(k) - T(1) + tmax(f, T(0))) * Tab<T>::acc_cell_min(A) * (T(1) - T(0x1p-20));
-  return tmax(m, r);
-}
-
-// SDF of the accelerated region through its uniform grid: min(margin, min
-// over the primitives listed in p's cell).  Equal to the region SDF where
-// that is below the margin, a lower bound elsewhere; outside the grid box
-// (which is the primitives' box grown by the margin) the distance to the
-// primitives' box is the lower bound.  Every index is checked.  Regions of
-// plain capsules read their compact records: from the workgroup's LDS
-// table when lds is given (FP32 staged walk), else from global memory.
-template <typename T, bool XF>
-__device__ __forceinline__ T accel_sdf(JobRef a, V3<T> p, LdsCaps lds = nullptr) {
-  const SMCRT_K Accel& A = kptr(a.sc)->acc;
-  const V3<T> lo = Tab<T>::acc_lo(A), ic = Tab<T>::acc_inv(A);
-  const T cx = (p.x - lo.x) * ic.x, cy = (p.y - lo.y) * ic.y, cz = (p.z - lo.z) * ic.z;
-  const int dx = A.dims[0], dy = A.dims[1], dz = A.dims[2];
-  if (!(cx >= T(0) && cy >= T(0) && cz >= T(0) && cx < T(dx) && cy < T(dy) && cz < T(dz))) {
-    const V3<T> bl = Tab<T>::acc_blo(A), bh = Tab<T>::acc_bhi(A);
-    const V3<T> o = mk(tmax(tmax(bl.x - p.x, p.x - bh.x), T(0)), tmax(tmax(bl.y - p.y, p.y - bh.y), T(0)),
-                       tmax(tmax(bl.z - p.z, p.z - bh.z), T(0)));
-    return tsqrt(dot(o, o));
-  }
-  int ix = (int)cx, iy = (int)cy, iz = (int)cz;
-  ix = ix < dx ? ix : dx - 1;
-  iy = iy < dy ? iy : dy - 1;
-  iz = iz < dz ? iz : dz - 1;
-  const int c = ix + dx * (iy + dy * iz);
-  const SMCRT_K uint32_t* offs = kptr(a.acc_offsets);
-  const SMCRT_K uint32_t* ids = kptr(a.acc_ids);
-  const uint32_t b = offs[c];
-  uint64_t e = offs[c + 1];
-  e = e < A.capacity ? e : A.capacity;
-  const SMCRT_K Prim<T>* P = Tab<T>::prims(a);
-  if (b >= e) return ring_bound<T>(a, A, c, cx, cy, cz, ix, iy, iz);
-  const uint32_t lo_id = (uint32_t)A.first_prim, hi_id = (uint32_t)(A.first_prim + A.n_prims);
-  T d = Tab<T>::acc_margin(A);
-  if (A.caps) {
-    if constexpr (sizeof(T) == 4) {
-      if (lds) {
-        for (uint64_t i = b; i < e; ++i) {
-          const uint32_t id = ids[i];
-          if (id >= lo_id && id < hi_id) {
-            const uint32_t k = id - lo_id;
-            const F4 x = lds[2 * k], y = lds[2 * k + 1];
-            d = tmin(d, cap_sdf<T>(x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w, p));
-          }
-        }
-        return d;
-      }
-    }
-    const SMCRT_K T* C = Tab<T>::caps(a);
-    for (uint64_t i = b; i < e; ++i) {
-      const uint32_t id = ids[i];
-      if (id >= lo_id && id < hi_id) {
-        const SMCRT_K T* c = C + 8 * (size_t)(id - lo_id);
-        d = tmin(d, cap_sdf<T>(c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7], p));
-      }
-    }
-    return d;
-  }
-  for (uint64_t i = b; i < e; ++i) {
-    const uint32_t id = ids[i];
-    if (id >= lo_id && id < hi_id) d = tmin(d, prim_sdf<T, XF>(P, (int)id, p));
-  }
-  return d;
-}
-
-// SDF of region r (through the grid when r is the accelerated region)
-template <typename T, bool XF>
-__device__ __forceinline__ T region_dist(JobRef a, int r, V3<T> p, LdsCaps lds = nullptr) {
-  if (r == a.acc_region) return accel_sdf<T, XF>(a, p, lds);
-  return region_sdf<T, XF>(a, kptr(a.sc)->reg[r], p);
-}
-
 // An evaluation record in scalar registers.
 typedef uint32_t U16 __attribute__((ext_vector_type(16)));
 template <typename T>
@@ -573,6 +525,7 @@ struct StepV<float> {
   U16 w;
   __device__ __forceinline__ int bits() const { return (int)w[0]; }
   __device__ __forceinline__ int index() const { return (int)w[1]; }
+  __device__ __forceinline__ uint32_t word(int i) const { return w[i & 15]; }
   __device__ __forceinline__ float operator[](int k) const { return __builtin_bit_cast(float, (uint32_t)w[2 + k]); }
   __device__ __forceinline__ float k() const { return (*this)[10]; }
   __device__ __forceinline__ float inv_k() const { return (*this)[11]; }
@@ -597,6 +550,127 @@ __device__ __forceinline__ StepV<double> load_step(const SMCRT_K StepRec<double>
   return {q[0], q[1]};
 }
 
+// What a query of the acceleration grid needs, from the scene header or from
+// the region's evaluation record.
+template <typename T>
+struct GridV {
+  V3<T> lo, ic;
+  T margin, cell_min;
+  int dx, dy, dz;
+  uint32_t first, n;
+  uint64_t capacity;
+  bool caps;
+};
+template <typename T>
+__device__ __forceinline__ GridV<T> grid_of(const SMCRT_K Accel& A) {
+  return {Tab<T>::acc_lo(A), Tab<T>::acc_inv(A), Tab<T>::acc_margin(A), Tab<T>::acc_cell_min(A), A.dims[0], A.dims[1],
+          A.dims[2], (uint32_t)A.first_prim, (uint32_t)A.n_prims, A.capacity, A.caps != 0};
+}
+template <typename T>
+__device__ __forceinline__ GridV<T> grid_of(const StepV<T>& r) {  // AccelRec
+  constexpr int w = 2 + 8 * (int)sizeof(T) / 4;
+  return {mk(r[0], r[1], r[2]), mk(r[3], r[4], r[5]), r[6], r[7], (int)r.word(w), (int)r.word(w + 1), (int)r.word(w + 2),
+          (uint32_t)r.index(), r.word(w + 3), (uint64_t)r.word(w + 4) | ((uint64_t)r.word(w + 5) << 32),
+          (r.bits() & kStepCaps) != 0};
+}
+
+// Lower bound of the accelerated region's SDF at p in a cell that lists no
+// primitive, from the cell's ring distance k (in cells) to the nearest cell
+// that lists one: every surface point lies in such a cell, so the surface is
+// at least k - 1 whole cells plus p's way to its own cell's faces away (the
+// smallest side counted; cell coordinates cx, cy, cz of p and its cell
+// ix, iy, iz).  Never below the margin; a relative 2^-20 less against
+// rounding.
+template <typename T>
+__device__ __forceinline__ T ring_bound(JobRef a, T margin, T cell_min, int c, T cx, T cy, T cz, int ix, int iy, int iz) {
+  if (a.acc_rings == nullptr) return margin;
+  const uint32_t k = kptr(a.acc_rings)[c];
+  const T fx = cx - T(ix), fy = cy - T(iy), fz = cz - T(iz);
+  const T f = tmin(tmin(tmin(fx, T(1) - fx), tmin(fy, T(1) - fy)), tmin(fz, T(1) - fz));
+  const T r = (T(k) - T(1) + tmax(f, T(0))) * cell_min * (T(1) - T(0x1p-20));
+  return tmax(margin, r);
+}
+
+// Where p lies in the grid of the accelerated region.  True when its cell
+// lists primitives: ids[*b, *e).  Else *d is the region's distance bound
+// there: outside the grid box (which is the primitives' box grown by the
+// margin) the distance to the primitives' box, in an empty cell its ring's.
+template <typename T>
+__device__ __forceinline__ bool grid_cell(JobRef a, const GridV<T>& G, V3<T> p, uint32_t* b, uint32_t* e, T* d) {
+  const T cx = (p.x - G.lo.x) * G.ic.x, cy = (p.y - G.lo.y) * G.ic.y, cz = (p.z - G.lo.z) * G.ic.z;
+  const int dx = G.dx, dy = G.dy, dz = G.dz;
+  if (!(cx >= T(0) && cy >= T(0) && cz >= T(0) && cx < T(dx) && cy < T(dy) && cz < T(dz))) {
+    const SMCRT_K Accel& A = kptr(a.sc)->acc;
+    const V3<T> bl = Tab<T>::acc_blo(A), bh = Tab<T>::acc_bhi(A);
+    const V3<T> o = mk(tmax(tmax(bl.x - p.x, p.x - bh.x), T(0)), tmax(tmax(bl.y - p.y, p.y - bh.y), T(0)),
+                       tmax(tmax(bl.z - p.z, p.z - bh.z), T(0)));
+    *d = tsqrt(dot(o, o));
+    return false;
+  }
+  int ix = (int)cx, iy = (int)cy, iz = (int)cz;
+  ix = ix < dx ? ix : dx - 1;
+  iy = iy < dy ? iy : dy - 1;
+  iz = iz < dz ? iz : dz - 1;
+  const int c = ix + dx * (iy + dy * iz);
+  const SMCRT_K uint32_t* offs = kptr(a.acc_offsets);
+  const uint32_t first = offs[c], last = offs[c + 1];
+  *b = first;
+  *e = (uint64_t)last < G.capacity ? last : (uint32_t)G.capacity;
+  if (*b < *e) return true;
+  *d = ring_bound<T>(a, G.margin, G.cell_min, c, cx, cy, cz, ix, iy, iz);
+  return false;
+}
+
+// SDF of the accelerated region through its uniform grid: min(margin, min
+// over the primitives listed in p's cell).  Equal to the region SDF where
+// that is below the margin, a lower bound elsewhere; outside the grid box
+// (which is the primitives' box grown by the margin) the distance to the
+// primitives' box is the lower bound.  Every index is checked.  Regions of
+// plain capsules read their compact records: from the workgroup's LDS
+// table when lds is given (FP32 staged walk), else from global memory.
+template <typename T, bool XF>
+__device__ __forceinline__ T accel_sdf(JobRef a, const GridV<T>& G, V3<T> p, LdsCaps lds = nullptr) {
+  uint32_t b, e;
+  T d;
+  if (!grid_cell<T>(a, G, p, &b, &e, &d)) return d;
+  const SMCRT_K uint32_t* ids = kptr(a.acc_ids);
+  d = G.margin;
+  if (G.caps) {
+    if constexpr (sizeof(T) == 4) {
+      if (lds) {
+        for (uint32_t i = b; i < e; ++i) {
+          const uint32_t id = ids[i] - G.first, k = id < G.n ? id : 0u;
+          const F4 x = lds[2 * k], y = lds[2 * k + 1];
+          const T v = cap_sdf<T>(x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w, p);
+          d = id < G.n ? tmin(d, v) : d;
+        }
+        return d;
+      }
+    }
+    const SMCRT_K T* C = Tab<T>::caps(a);
+    for (uint32_t i = b; i < e; ++i) {
+      const uint32_t id = ids[i] - G.first, k = id < G.n ? id : 0u;
+      const SMCRT_K T* c = C + 8 * (size_t)k;
+      const T v = cap_sdf<T>(c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7], p);
+      d = id < G.n ? tmin(d, v) : d;
+    }
+    return d;
+  }
+  const SMCRT_K Prim<T>* P = Tab<T>::prims(a);
+  for (uint32_t i = b; i < e; ++i) {
+    const uint32_t id = ids[i];
+    if (id - G.first < G.n) d = tmin(d, prim_sdf<T, XF, false>(P, (int)id, p));
+  }
+  return d;
+}
+
+// SDF of region r (through the grid when r is the accelerated region)
+template <typename T, bool XF>
+__device__ __forceinline__ T region_dist(JobRef a, int r, V3<T> p, LdsCaps lds = nullptr) {
+  if (r == a.acc_region) return accel_sdf<T, XF>(a, grid_of<T>(kptr(a.sc)->acc), p, lds);
+  return region_sdf<T, XF>(a, kptr(a.sc)->reg[r], p);
+}
+
 // Distance of p to the nearest surface: the smallest |region_dist| over the
 // regions, by the scene's evaluation records.  A lone wave waits for every
 // scalar load it needs; walked through the region, then its primitive's kind,
@@ -614,10 +688,10 @@ __device__ __forceinline__ T walk_distance(JobRef a, const SMCRT_K StepRec<T>* r
     const StepV<T> next = load_step(rec + (more ? i : 0));
     const int bits = cur.bits(), kind = bits & kStepKind, op = bits >> kStepOp;
     if (kind == kStepAccel) {
-      d = accel_sdf<T, XF>(a, p, lds);
+      d = accel_sdf<T, XF>(a, grid_of<T>(cur), p, lds);
     } else {
       T b;
-      if (XF && (bits & kStepPlaced)) b = placed_prim_sdf<T>(Tab<T>::prims(a), cur.index(), p);
+      if (XF && (bits & kStepPlaced)) b = placed_prim<T>(Tab<T>::prims(a), cur.index(), p);
       else b = shape_of<T>(kind, cur, p);
       if (bits & kStepFirst) {
         d = b;
@@ -682,10 +756,11 @@ __device__ __forceinline__ int volume_face(ScP sc, V3<T> p) {
 // lies between its planes.)
 template <typename T>
 __device__ __forceinline__ T ambient_free(ScP sc, int nr, V3<T> p, V3<T> u, T delta) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  // keep the divisions here: few steps come this way
-  asm volatile("" : "+v"(u.x), "+v"(u.y), "+v"(u.z));
-#endif
+  // (the compiler would take the divisions out of the loop of steps, few of
+  // which come this way)
+  hold(u.x);
+  hold(u.y);
+  hold(u.z);
   const V3<T> c = Tab<T>::bb_c(sc), h = Tab<T>::bb_h(sc);
   const T pv[3] = {p.x, p.y, p.z}, uv[3] = {u.x, u.y, u.z};
   const T cv[3] = {c.x, c.y, c.z}, hv[3] = {h.x, h.y, h.z};
@@ -800,7 +875,7 @@ __device__ __forceinline__ T accel_seg(JobRef a, V3<T> p, V3<T> u, T err, T* tb)
   const T cx = (p.x - lo.x) * ic.x, cy = (p.y - lo.y) * ic.y, cz = (p.z - lo.z) * ic.z;
   const int dx = A.dims[0], dy = A.dims[1], dz = A.dims[2];
   if (rule != kSegUnion || !(cx >= T(0) && cy >= T(0) && cz >= T(0) && cx < T(dx) && cy < T(dy) && cz < T(dz))) {
-    const T d = accel_sdf<T, XF>(a, p);
+    const T d = accel_sdf<T, XF>(a, grid_of<T>(A), p);
     *tb = tabs(d);
     return d;
   }
@@ -815,7 +890,7 @@ __device__ __forceinline__ T accel_seg(JobRef a, V3<T> p, V3<T> u, T err, T* tb)
   uint64_t e = offs[cell + 1];
   e = e < A.capacity ? e : A.capacity;
   if (b >= e) {
-    const T d = ring_bound<T>(a, A, cell, cx, cy, cz, ix, iy, iz);
+    const T d = ring_bound<T>(a, Tab<T>::acc_margin(A), Tab<T>::acc_cell_min(A), cell, cx, cy, cz, ix, iy, iz);
     *tb = d;
     return d;
   }
@@ -948,7 +1023,7 @@ struct Lane {
   WaveStage* stage; // this wave's staging area (LDS)
   double abs_sum;   // absorbed weight not yet added to the workgroup sums
   int abs_region;
-  uint32_t n_steps, n_inter, n_pieces, n_atomics;
+  uint32_t n_steps, n_inter, n_pieces, n_atomics;  // (pieces and atomics: the voxel model's)
   // trace
   smcrt_event* rec;
   int n_rec;
@@ -974,8 +1049,8 @@ __device__ __forceinline__ void stage_add(double* F, WaveStage& S, int v, double
   }
 }
 
-// Adds the staged entries to F once at least min_count are waiting.  Called
-// with every lane of the wave active.
+// Adds the staged entries to F once at least min_count are waiting (voxel
+// model).  Called with every lane of the wave active.
 __device__ __forceinline__ void stage_drain(double* F, WaveStage& S, int min_count, int lane) {
   const int cnt = __builtin_amdgcn_readfirstlane(S.n);
   if (cnt > 0 && cnt >= min_count) {
@@ -1057,54 +1132,6 @@ __device__ __forceinline__ DdaAxis<T> start_axis(T g, T gu, T r, int n, T t0) {
   A.tn = gu > T(0) ? (T(k + 1) - g) * r : (gu < T(0) ? (T(k) - g) * r : tinf<T>());
   A.dt = gu != T(0) ? tabs(r) : tinf<T>();
   return A;
-}
-
-// Path-length estimator (Sec. 3.1): weight * length of the straight move
-// p -> p + len*u credited to every voxel it crosses, by a 3-D DDA in voxel
-// units.  Voxel i spans [lo + i*D, lo + (i+1)*D); indices are clamped on
-// entry and the walk stops when it steps off the grid.  The axes are kept
-// in named registers and the linear voxel index is stepped by the axis
-// stride, so a crossing costs a few compares and selects.
-template <typename T>
-__device__ __forceinline__ void tally_move(JobRef a, V3<T> p, V3<T> u, T len, double w, Lane& ln) {
-  ScP sc = fresh(kptr(a.sc));
-  if (a.fluence == nullptr || !(len > T(0))) return;
-  const int nx = sc->g_dims[0], ny = sc->g_dims[1], nz = sc->g_dims[2];
-  const V3<T> inv = Tab<T>::g_inv(sc);
-  const V3<T> lo = Tab<T>::g_lo(sc);
-  const T gx = (p.x - lo.x) * inv.x, gy = (p.y - lo.y) * inv.y, gz = (p.z - lo.z) * inv.z;
-  const T ux = u.x * inv.x, uy = u.y * inv.y, uz = u.z * inv.z;
-  if (!__builtin_isfinite(gx + gy + gz + ux + uy + uz + len)) return;
-  const T rx = trcp(ux), ry = trcp(uy), rz = trcp(uz);
-  T t0 = T(0), t1 = len;
-  if (!clip_axis(gx, ux, rx, nx, t0, t1) || !clip_axis(gy, uy, ry, ny, t0, t1) || !clip_axis(gz, uz, rz, nz, t0, t1))
-    return;
-  if (!(t1 > t0)) return;
-  DdaAxis<T> X = start_axis(gx, ux, rx, nx, t0), Y = start_axis(gy, uy, ry, ny, t0),
-             Z = start_axis(gz, uz, rz, nz, t0);
-  int lin = X.i + nx * (Y.i + ny * Z.i);
-  const int sy = Y.s * nx, sz = Z.s * (nx * ny);
-  T t = t0;
-  const int cap = nx + ny + nz + 3;
-  for (int it = 0; it < cap; ++it) {
-    const T tn = tmin(tmin(X.tn, Y.tn), tmin(Z.tn, t1));
-    const T piece = tn - t;
-    if (piece > T(0)) run_add(a.fluence, ln, a.brick ? brick_index(X.i, Y.i, Z.i, nx, ny) : lin, w * (double)piece);
-    if (tn >= t1) break;
-    // cross the nearest plane (ties: x before y before z)
-    const bool bx = X.tn <= Y.tn && X.tn <= Z.tn;
-    const bool by = !bx && Y.tn <= Z.tn;
-    const bool bz = !bx && !by;
-    X.i += bx ? X.s : 0;
-    Y.i += by ? Y.s : 0;
-    Z.i += bz ? Z.s : 0;
-    X.tn = bx ? X.tn + X.dt : X.tn;
-    Y.tn = by ? Y.tn + Y.dt : Y.tn;
-    Z.tn = bz ? Z.tn + Z.dt : Z.tn;
-    lin += bx ? X.s : (by ? sy : sz);
-    if ((unsigned)X.i >= (unsigned)nx || (unsigned)Y.i >= (unsigned)ny || (unsigned)Z.i >= (unsigned)nz) break;
-    t = tn;
-  }
 }
 
 // Unpolarised Fresnel reflectance between indices n1 -> n2 at incidence
@@ -1328,11 +1355,135 @@ __device__ __forceinline__ T step_along(Packet<T>& pk, T len) {
   return len;
 }
 
+// What the SDF walk's tally keeps per wave, in scalar registers: entries
+// waiting in the stage, and the counts of pieces and of additions issued.
+struct WaveTally {
+  int n;
+  unsigned long long pieces, atomics;
+};
+
+// Adds the SDF walk's staged entries to F once at least min_count are waiting.
+__device__ __forceinline__ void tally_drain(double* F, WaveStage& S, WaveTally& wt, int min_count, int lane) {
+  if (wt.n > 0 && wt.n >= min_count) {
+    for (int i = lane; i < wt.n; i += 64) grid_add(F, S.v[i], S.val[i]);
+    wt.n = 0;
+  }
+}
+
+// c ? a : b of values (between variables of an enclosing scope the operator
+// picks one of their addresses, which keeps them in memory)
+__device__ __forceinline__ int pick(bool c, int a, int b) { return c ? a : b; }
+
+// Path-length estimator (Sec. 3.1): weight * length of the packet's pending
+// straight path, which ends at its position, credited to every voxel it
+// crosses, by a 3-D DDA in voxel units.  Voxel i spans [lo + i*D, lo +
+// (i+1)*D); indices are clamped on entry and the walk stops when it steps off
+// the grid.  Called with every lane of the wave active; the lanes with want
+// set credit their paths together.
+//
+// A crossing is some forty vector instructions, and what bounds the tally is
+// the wave's wait for its longest path, so the loop is one straight body for
+// all lanes: no lane mask but a flag, the axes in named registers, the voxel
+// index stepped by the axis stride, and the number of staged entries in a
+// scalar register (ends of runs take their places in the stage by a ballot;
+// read from LDS at each run, it was a chain of two LDS accesses per piece).
+// Consecutive pieces of one path are in different voxels: only the first can
+// continue the lane's run.  (With the walk's steps in one straight body too:
+// 64 runs of 1e5 packets in a batch 41.0 to 38.2 ms, 1e4 packets of the vessel
+// scene 11.5 to 9.7, 1e5 packets of the 50^3 sphere 5.0 to 4.2; 1e7 packets of
+// the slab, bound by the additions themselves, 295 both ways.)
+template <typename T, bool BRICK>
+__device__ __forceinline__ void tally_pieces(double* F, WaveStage& S, WaveTally& wt, Run& run, bool active, int lin,
+                                             DdaAxis<T> X, DdaAxis<T> Y, DdaAxis<T> Z, int nx, int ny, int nz, T t, T t1,
+                                             double w) {
+  // steps left on each axis before the path is off the grid
+  int rx = X.s > 0 ? nx - 1 - X.i : X.i, ry = Y.s > 0 ? ny - 1 - Y.i : Y.i, rz = Z.s > 0 ? nz - 1 - Z.i : Z.i;
+  // index steps; bricks: inside the brick, and across its face (a step is
+  // inside when the index bit of the axis is clear moving up, set moving down)
+  const int by_n = (ny + 1) >> 1, bx_n = (nx + 1) >> 1;
+  const int ix = X.s, iy = BRICK ? Y.s * 2 : Y.s * nx, iz = BRICK ? Z.s * 4 : Z.s * (nx * ny);
+  const int ox = X.s * 7, oy = Y.s * (8 * bx_n - 2), oz = Z.s * (8 * bx_n * by_n - 4);
+  const int down = (X.s < 0 ? 1 : 0) | (Y.s < 0 ? 2 : 0) | (Z.s < 0 ? 4 : 0);
+  auto piece = [&](bool first) __attribute__((always_inline)) {
+    const T m = tmin(X.tn, tmin(Y.tn, Z.tn)), tn = tmin(m, t1);
+    const T len = tn - t;
+    const double val = w * (double)len;
+    const bool some = active && len > T(0);
+    const bool same = first && lin == run.v;
+    const bool push = some && !same && run.v >= 0;
+    const uint64_t ends = __ballot(push);
+    if (ends != 0ull) {
+      const int n = __popcll(ends);
+      if (wt.n + n <= kStage) {
+        const int at = wt.n + __builtin_amdgcn_mbcnt_hi((uint32_t)(ends >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ends, 0u));
+        if (push) {
+          S.v[at] = run.v;
+          S.val[at] = run.sum;
+        }
+        wt.n += n;
+      } else if (push) {
+        grid_add(F, run.v, run.sum);
+      }
+      wt.atomics += (unsigned long long)n;
+    }
+    wt.pieces += (unsigned long long)__popcll(__ballot(some));
+    const double sum = same ? run.sum + val : val;
+    run.sum = some ? sum : run.sum;
+    run.v = some ? lin : run.v;
+    // cross the nearest plane (ties: x before y before z)
+    const bool bx = X.tn == m, by = !bx && Y.tn == m, bz = !bx && !by;
+    int step = pick(bx, ix, pick(by, iy, iz));
+    if constexpr (BRICK) {
+      const int out = pick(bx, ox, pick(by, oy, oz)), bit = bx ? 1 : (by ? 2 : 4);
+      step = pick(((lin ^ down) & bit) != 0, out, step);
+    }
+    lin += step;
+    X.tn = bx ? X.tn + X.dt : X.tn;
+    Y.tn = by ? Y.tn + Y.dt : Y.tn;
+    Z.tn = bz ? Z.tn + Z.dt : Z.tn;
+    rx -= bx ? 1 : 0;
+    ry -= by ? 1 : 0;
+    rz -= bz ? 1 : 0;
+    t = tn;
+    active = active && tn < t1 && (rx | ry | rz) >= 0;
+  };
+  piece(true);
+  while (__ballot(active) != 0ull) piece(false);
+}
+
 template <typename T>
-__device__ __forceinline__ void flush_tally(JobRef a, Packet<T>& pk, Lane& ln) {
-  if (pk.pend > T(0))
-    tally_move<T>(a, pk.p - pk.pend * pk.u, pk.u, pk.pend, pk.w, ln);
-  pk.pend = T(0);
+__device__ __forceinline__ void tally_path(JobRef a, const Packet<T>& pk, bool want, Lane& ln, WaveTally& wt) {
+  if (a.fluence == nullptr || __ballot(want) == 0ull) return;
+  ScP sc = fresh(kptr(a.sc));
+  const int nx = sc->g_dims[0], ny = sc->g_dims[1], nz = sc->g_dims[2];
+  DdaAxis<T> X{0, 0, T(0), T(0)}, Y = X, Z = X;
+  T t0 = T(0), t1 = T(0);
+  bool active = false;
+  if (want) {
+    const V3<T> inv = Tab<T>::g_inv(sc);
+    const V3<T> lo = Tab<T>::g_lo(sc);
+    const T len = pk.pend;
+    const V3<T> u = pk.u, p = pk.p - len * u;
+    const T gx = (p.x - lo.x) * inv.x, gy = (p.y - lo.y) * inv.y, gz = (p.z - lo.z) * inv.z;
+    const T ux = u.x * inv.x, uy = u.y * inv.y, uz = u.z * inv.z;
+    if (__builtin_isfinite(gx + gy + gz + ux + uy + uz + len)) {
+      const T rx = trcp(ux), ry = trcp(uy), rz = trcp(uz);
+      t1 = len;
+      if (clip_axis(gx, ux, rx, nx, t0, t1) && clip_axis(gy, uy, ry, ny, t0, t1) && clip_axis(gz, uz, rz, nz, t0, t1) &&
+          t1 > t0) {
+        X = start_axis(gx, ux, rx, nx, t0);
+        Y = start_axis(gy, uy, ry, ny, t0);
+        Z = start_axis(gz, uz, rz, nz, t0);
+        active = true;
+      }
+    }
+  }
+  if (a.brick)
+    tally_pieces<T, true>(a.fluence, *ln.stage, wt, ln.run, active, brick_index(X.i, Y.i, Z.i, nx, ny), X, Y, Z, nx, ny, nz,
+                          t0, t1, pk.w);
+  else
+    tally_pieces<T, false>(a.fluence, *ln.stage, wt, ln.run, active, X.i + nx * (Y.i + ny * Z.i), X, Y, Z, nx, ny, nz, t0,
+                           t1, pk.w);
 }
 
 // Escape image (Sec. 3.2 and Sec. 5: the light at a single plane of
@@ -1533,8 +1684,11 @@ __device__ __forceinline__ bool stage_caps(JobRef a, F4* dst) {
 
 // Adds a wave's pending sums to job a's outputs and clears them.  Called with
 // every lane of the wave active.
-__device__ __forceinline__ void flush_wave(JobRef a, Lane& ln, LdsTallies& L, int lane) {
-  if (a.fluence != nullptr) stage_drain(a.fluence, *ln.stage, 1, lane);
+__device__ __forceinline__ void flush_wave(JobRef a, Lane& ln, WaveTally& wt, LdsTallies& L, int lane) {
+  if (a.fluence != nullptr) {
+    stage_drain(a.fluence, *ln.stage, 1, lane);
+    tally_drain(a.fluence, *ln.stage, wt, 1, lane);
+  }
   if (ln.run.v >= 0) {
     grid_add(a.fluence, ln.run.v, ln.run.sum);
     ++ln.n_atomics;
@@ -1544,6 +1698,11 @@ __device__ __forceinline__ void flush_wave(JobRef a, Lane& ln, LdsTallies& L, in
   atomicAdd(&L.cnt[kCInteractions], (unsigned long long)ln.n_inter);
   atomicAdd(&L.cnt[kCPieces], (unsigned long long)ln.n_pieces);
   atomicAdd(&L.cnt[kCAtomics], (unsigned long long)ln.n_atomics);
+  if (lane == 0) {
+    L.cnt[kCPieces] += wt.pieces;
+    L.cnt[kCAtomics] += wt.atomics;
+  }
+  wt.pieces = wt.atomics = 0ull;
   ln.run.v = -1;
   ln.run.sum = 0.0;
   ln.abs_region = -1;

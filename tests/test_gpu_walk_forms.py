@@ -106,3 +106,48 @@ def test_grid_builds_at_the_edges_of_the_scan_tiles(S, eng, W, cells, n_caps):
     far = ~near & inside
     assert np.all(a[far] >= margin * (1 - 1e-12))
     assert np.array_equal(own, own_a)
+
+
+@pytest.mark.parametrize("dims", [(1, 1, 1), (2, 1, 3), (33, 7, 2), (5, 64, 31), (127, 129, 128)])
+def test_tally_over_grids_and_layouts(S, eng, orc, W, dims):
+    """straight absorbed paths through odd grids that the ball overlaps in
+    part; at the finest one a wave's pieces overflow its staging area.  FP64
+    against the oracle to rounding (positions of size 1, a few hundred
+    additions per voxel); FP32 bricks against FP32 linear storage: the same
+    pieces in another order."""
+    desc = W.absorbing_sphere(mua=0.8)
+    desc["grid"] = {"lo": [-1.2, -0.9, -1.0], "hi": [0.95, 1.1, 1.05], "dims": list(dims)}
+    n = 1000
+    o = orc.run(desc, 21, n)
+    layouts = [S.Engine(0, tally_layout=k) for k in (0, 1)]
+    scale = o["fluence_raw"].max()
+    for e in layouts:
+        g = S.run(desc, 21, n, engine=e, precision="f64")
+        assert np.max(np.abs(g["fluence_raw"] - o["fluence_raw"])) <= 1e-12 * scale
+    a, b = [S.run(desc, 21, n, engine=e, precision="f32") for e in layouts]
+    assert a["voxel_pieces"] == b["voxel_pieces"]
+    assert np.max(np.abs(a["fluence_raw"] - b["fluence_raw"])) <= 1e-12 * scale
+    assert abs(a["fluence_raw"].sum() - o["fluence_raw"].sum()) <= 1e-4 * o["fluence_raw"].sum()
+    for e in layouts:
+        e.close()
+
+
+@pytest.mark.parametrize("relax", [1.0, 1.7])
+@pytest.mark.parametrize("placed", [False, True])
+def test_accelerated_unions_in_every_kernel(S, eng, orc, W, relax, placed):
+    """vessels through the grid, plain and over-relaxed (another kernel), with
+    and without a placed member (another again), against the oracle"""
+    plain = W.vessel_scene(2, n_caps=60, n_grid=8)
+    if placed:
+        p = plain["prims"][plain["regions"][1]["prims"][0]]
+        p["transform"] = {"R": W.rotation([0.0, 0.0, 1.0], 0.0), "t": [0.0, 0.0, 0.0], "s": 1.0}
+    desc = dict(plain, relax=relax)
+    n = 200
+    mut = [rg["mua"] + rg["mus"] for rg in desc["regions"]]
+    o = [orc.trace(plain, 13, pid, 40) for pid in range(n)]
+    g = S.trace(desc, 13, list(range(n)), 40, engine=eng, precision="f64")
+    frac, worst, bad = compare_traces(o, g, extent_of(S, desc), 1e-6, cap=40, mut=mut)
+    assert frac >= 0.98, (frac, worst, bad[:5])  # grazing near-ties
+    k, t = S.run(desc, 13, 3000, engine=eng, precision="f64"), S.run(plain, 13, 3000, engine=eng, precision="f64")
+    assert abs(identity_residual(k)) <= 1e-9 * 3000
+    assert abs(k["interactions"] - t["interactions"]) <= 2e-3 * t["interactions"]
