@@ -231,7 +231,7 @@ struct Tab<double> {
 // x^2 + y^2 with its one rounding fixed in FP32 (which product the compiler
 // would fuse depends on the code around it; results do not)
 __device__ __forceinline__ float sum_sq(float x, float y) { return __builtin_fmaf(x, x, y * y); }
-__device__ __forceinline__ double sum_sq(double x, double y) { return x * x + y * y; }
+__device__ __forceinline__ double sum_sq(double x, double y) { return __builtin_fma(x, x, y * y); }
 
 // exact Euclidean SDF of one primitive's shape in its own frame (Sec. 2.2;
 // Eq. 3 for the sphere)
@@ -482,6 +482,14 @@ __device__ __forceinline__ T prim_sdf(const SMCRT_K Prim<T>* P, int i, V3<T> p) 
   return shape_sdf(P, i, p);
 }
 
+// polynomial smooth union of two distances, its roundings fixed like fdot's
+template <typename T>
+__device__ __forceinline__ T smooth_min(T d, T b, T k, T inv_k) {
+  const T h = tclamp(tfma(T(0.5) * (b - d), inv_k, T(0.5)), T(0), T(1));
+  const T g = T(1) - h;
+  return tfma(-(k * h), g, tfma(h, d, g * b));
+}
+
 // region SDF from its primitives in order (CSG of Sec. 2.2): union (min),
 // polynomial smooth union, intersection (max) or difference, the first
 // primitive minus the others (max(d, -d_i)).  Intersection and difference
@@ -495,8 +503,7 @@ __device__ __forceinline__ T region_sdf(JobRef a, RegRef R, V3<T> p) {
   for (int i = 1; i < R.count; ++i) {
     const T b = prim_sdf<T, XF>(P, R.first + i, p);
     if (op == kSmoothUnion) {
-      const T h = tclamp(T(0.5) + T(0.5) * (b - d) * Tab<T>::inv_k(R), T(0), T(1));
-      d = h * d + (T(1) - h) * b - Tab<T>::k(R) * h * (T(1) - h);
+      d = smooth_min(d, b, Tab<T>::k(R), Tab<T>::inv_k(R));
     } else {
       const T nb = op == kSubtract ? -b : b;
       d = op == kUnion ? tmin(d, nb) : tmax(d, nb);
@@ -696,8 +703,7 @@ __device__ __forceinline__ T walk_distance(JobRef a, const SMCRT_K StepRec<T>* r
       if (bits & kStepFirst) {
         d = b;
       } else if (op == kSmoothUnion) {
-        const T h = tclamp(T(0.5) + T(0.5) * (b - d) * cur.inv_k(), T(0), T(1));
-        d = h * d + (T(1) - h) * b - cur.k() * h * (T(1) - h);
+        d = smooth_min(d, b, cur.k(), cur.inv_k());
       } else {
         const T nb = op == kSubtract ? -b : b;
         d = op == kUnion ? tmin(d, nb) : tmax(d, nb);

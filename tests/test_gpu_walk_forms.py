@@ -151,3 +151,25 @@ def test_accelerated_unions_in_every_kernel(S, eng, orc, W, relax, placed):
     k, t = S.run(desc, 13, 3000, engine=eng, precision="f64"), S.run(plain, 13, 3000, engine=eng, precision="f64")
     assert abs(identity_residual(k)) <= 1e-9 * 3000
     assert abs(k["interactions"] - t["interactions"]) <= 2e-3 * t["interactions"]
+
+
+@pytest.mark.parametrize("name", ["vessels", "gallery", "cylinder"])
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_point_queries_at_the_edges_of_their_kernels(S, eng, W, name, precision):
+    """the same points asked for in calls of every size where the division of
+    the work changes (waves of 64, a workgroup of 256, a point per lane from
+    2^17 on): the same evaluations, so equal to rounding -- distances of size
+    1, normals from differences over a step of 1e-5 or so"""
+    desc = W.vessel_scene(1, n_caps=20, n_grid=8) if name == "vessels" else W.WORKLOADS[name](8)
+    lo, hi = np.array(desc["grid"]["lo"]), np.array(desc["grid"]["hi"])
+    pts = np.random.default_rng(4).uniform(lo - 0.05, hi + 0.05, (131072, 3))
+    d0, own0, nrm0 = S.distance(desc, pts, engine=eng, precision=precision, normals=True)
+    for n in (1, 63, 64, 65, 255, 257, 5000, 131071):
+        d, own, nrm = S.distance(desc, pts[:n], engine=eng, precision=precision, normals=True)
+        assert np.max(np.abs(d - d0[:n])) <= (1e-14 if precision == "f64" else 1e-6)
+        far = np.abs(d0[:n]).min(axis=1) > 1e-5
+        assert np.array_equal(own[far], own0[:n][far])
+        both = np.isfinite(nrm) & np.isfinite(nrm0[:n])
+        assert np.mean(both) > 0.99 and np.max(np.abs(nrm - nrm0[:n])[both]) <= 1e-8
+        e, own_e = S.distance(desc, pts[:n], engine=eng, precision=precision)
+        assert np.max(np.abs(e - d)) <= (1e-14 if precision == "f64" else 1e-6)
