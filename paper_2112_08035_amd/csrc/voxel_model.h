@@ -38,7 +38,7 @@ template <typename T, bool TRACE>
 __device__ __forceinline__ void escape_face(JobRef a, Packet<T>& pk, Lane& ln, LdsTallies& L, int face, bool on_grid) {
   ScP sc = kptr(a.sc);
   pk.region = sc->n_regions;
-  atomicAdd(&L.escaped[face], pk.w);
+  atomicAdd(&L.sum[kSEscaped + face], pk.w);
   atomicAdd(&L.cnt[kCEscapes], 1ull);
   if (on_grid) detect<T>(a, pk, face, (face & 1) ? Tab<T>::g_hi(sc, face >> 1) : Tab<T>::g_lo(sc, face >> 1));
   record<T, TRACE>(a, pk, ln, SMCRT_EV_ESCAPE);
@@ -161,7 +161,7 @@ __device__ bool voxel_step(JobRef a, Regions<T> rg, Packet<T>& pk, int v[3], Lan
                            uint32_t max_events) {
   ScP sc = kptr(a.sc);
   if (++pk.steps > max_steps || pk.k > max_events) {
-    atomicAdd(&L.stalled, pk.w);
+    atomicAdd(&L.sum[kSStalled], pk.w);
     atomicAdd(&L.cnt[kCStalls], 1ull);
     record<T, TRACE>(a, pk, ln, SMCRT_EV_STALL);
     return false;
@@ -211,7 +211,7 @@ __device__ bool voxel_step(JobRef a, Regions<T> rg, Packet<T>& pk, int v[3], Lan
   }
   if (!voxel_interface<T, TRACE>(a, rg, pk, ln, L, ax, r2, n1, n2)) return true;  // reflected: same voxel
   if (off) {  // transmitted out of the grid
-    atomicAdd(&L.escaped[face], pk.w);
+    atomicAdd(&L.sum[kSEscaped + face], pk.w);
     atomicAdd(&L.cnt[kCEscapes], 1ull);
     detect<T>(a, pk, face, (face & 1) ? Tab<T>::g_hi(sc, face >> 1) : Tab<T>::g_lo(sc, face >> 1));
     record<T, TRACE>(a, pk, ln, SMCRT_EV_ESCAPE);

@@ -316,14 +316,8 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
   LdsTallies& L = Lw[wib];
   RegionRow<T>* rows = Rw[STAGE ? 0 : wib];
   const Regions<T> rg = (Regions<T>)rows;
-  if (lane == 0) {
-    Sw[wib].n = 0;
-    for (int r = 0; r < kMaxRegions; ++r) L.absorbed[r] = 0.0;
-    for (int f = 0; f < 6; ++f) L.escaped[f] = 0.0;
-    for (int c = 0; c < 16; ++c) L.cnt[c] = 0ull;
-    L.gain = L.loss = L.stalled = 0.0;
-  }
-  __threadfence_block();
+  if (lane == 0) Sw[wib].n = 0;
+  clear_tallies(L, lane);
 
   Lane ln;
   ln.stage = &Sw[wib];
@@ -554,7 +548,7 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
                 }
               }
               if (stall) {
-                atomicAdd(&L.stalled, pk.w);
+                atomicAdd(&L.sum[kSStalled], pk.w);
                 atomicAdd(&L.cnt[kCStalls], 1ull);
                 record<T, TRACE>(a, pk, ln, SMCRT_EV_STALL);
                 pk.state = kDead;
@@ -565,7 +559,7 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
                 move = false;
               } else if (outside) {  // outside the simulation volume
                 const int face = volume_face<T>(sc, pk.p);
-                atomicAdd(&L.escaped[face], pk.w);
+                atomicAdd(&L.sum[kSEscaped + face], pk.w);
                 atomicAdd(&L.cnt[kCEscapes], 1ull);
                 detect<T>(a, pk, face, Tab<T>::bb_c(sc, face >> 1) + ((face & 1) ? Tab<T>::bb_h(sc, face >> 1) : -Tab<T>::bb_h(sc, face >> 1)));
                 record<T, TRACE>(a, pk, ln, SMCRT_EV_ESCAPE);
