@@ -68,7 +68,25 @@ __device__ __forceinline__ V3<double> to_d(V3<T> a) { return {(double)a.x, (doub
 template <typename T>
 __device__ __forceinline__ V3<T> from_d(V3<double> a) { return {(T)a.x, (T)a.y, (T)a.z}; }
 
-__device__ __forceinline__ float tsqrt(float x) { return __builtin_sqrtf(x); }
+// Correctly rounded like sqrtf from 2^-96 up: the instruction's result (1 ulp)
+// or a neighbour, by the signs of the residuals.  sqrtf also scales its
+// operand against underflow of the residual and picks out 0 and infinity,
+// which here come through the comparisons as they are.  Below 2^-96 (lengths
+// under 4e-15) the result may be 1 ulp off, and a denormal operand gives
+// nearly zero.  9 instructions for 16, on the chain of every step: 1e5 packets
+// of the 50^3 sphere 3.86 to 3.69 ms, 1e6 of the reflectance image 20.2 to
+// 19.4, 1e4 of the vessel scene 9.5 to 9.0, 2e5 of the gallery 49.9 to 48.2.
+__device__ __forceinline__ float tsqrt(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const float s = __builtin_amdgcn_sqrtf(x);
+  const float lo = __builtin_bit_cast(float, __builtin_bit_cast(int, s) - 1);
+  const float hi = __builtin_bit_cast(float, __builtin_bit_cast(int, s) + 1);
+  const float r = __builtin_fmaf(-lo, s, x) <= 0.0f ? lo : s;
+  return __builtin_fmaf(-hi, s, x) > 0.0f ? hi : r;
+#else
+  return __builtin_sqrtf(x);
+#endif
+}
 __device__ __forceinline__ double tsqrt(double x) { return __builtin_sqrt(x); }
 __device__ __forceinline__ float tlog(float x) { return __logf(x); }
 __device__ __forceinline__ double tlog(double x) { return log(x); }

@@ -173,3 +173,17 @@ def test_point_queries_at_the_edges_of_their_kernels(S, eng, W, name, precision)
         assert np.mean(both) > 0.99 and np.max(np.abs(nrm - nrm0[:n])[both]) <= 1e-8
         e, own_e = S.distance(desc, pts[:n], engine=eng, precision=precision)
         assert np.max(np.abs(e - d)) <= (1e-14 if precision == "f64" else 1e-6)
+
+
+def test_fp32_lengths_are_correctly_rounded(S, eng, W):
+    """the FP32 distance of a sphere about the origin, on an axis, is
+    sqrt(x x) - r with one rounding each: float32 arithmetic, bit by bit"""
+    desc = W.absorbing_sphere(r=1.0)
+    x = np.concatenate([np.geomspace(1e-12, 1e12, 30000), np.random.default_rng(2).uniform(0.5, 2.0, 30000)])
+    x = x.astype(np.float32)
+    pts = np.zeros((x.size, 3))
+    for axis in range(3):
+        pts[:] = 0.0
+        pts[:, axis] = x
+        d, _ = S.distance(desc, pts, engine=eng, precision="f32")
+        assert np.array_equal(d[:, 0].astype(np.float32), np.sqrt(x * x) - np.float32(1.0))
