@@ -187,3 +187,24 @@ def test_fp32_lengths_are_correctly_rounded(S, eng, W):
         pts[:, axis] = x
         d, _ = S.distance(desc, pts, engine=eng, precision="f32")
         assert np.array_equal(d[:, 0].astype(np.float32), np.sqrt(x * x) - np.float32(1.0))
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("u", [[0.0, 0.0, -1.0], [0.0, -1.0, 0.0], [1.0, 0.0, 0.0], [0.0, -0.6, 0.8]])
+def test_tally_of_rays_along_voxel_planes(S, eng, orc, W, u, precision):
+    """pencil beams parallel to axes, in a grid's outer faces, in planes
+    between voxels, inside and outside: against the oracle, exactly placed
+    (steps of 1/8: no rounding in FP32 either) up to the absorbed lengths"""
+    for x in (-0.5, -0.25, 0.125, 0.5, 0.625):
+        desc = W.absorbing_sphere(mua=0.5)
+        desc["prims"] = [{"kind": "box", "c": [0.0, 0.0, 0.0], "half": [1.0] * 3}]
+        p = [x, -x, x]
+        for i in range(3):
+            if u[i] != 0.0:
+                p[i] = 0.0
+        desc["source"] = {"kind": "pencil", "p": p, "u": u}
+        desc["grid"] = {"lo": [-0.5] * 3, "hi": [0.5] * 3, "dims": [4, 8, 4]}
+        n = 500
+        o, g = orc.run(desc, 3, n), S.run(desc, 3, n, engine=eng, precision=precision)
+        eps = 1e-12 if precision == "f64" else 1e-5  # of lengths of size 1, n of them
+        assert np.max(np.abs(g["fluence_raw"] - o["fluence_raw"])) <= eps * n, (x, u)
