@@ -152,51 +152,108 @@ __device__ bool enter_grid(JobRef a, Regions<T> rg, Packet<T>& pk, int v[3], Lan
   return false;
 }
 
-// One move of the voxel walk: to the exit face of voxel v or to the
-// interaction point, whichever is nearer, tallying the piece.  Sets
-// pk.state = kInteract when the optical depth runs out.  Returns false when
-// the packet has ended (escape or step cap).
+// x / u, y = 1 / u: corrections of x y by its residual (Markstein), the last
+// steps of a division without its own reciprocal
+template <typename T>
+__device__ __forceinline__ T div_by(T x, T u, T y) {
+  T q = x * y;
+  q = tfma(tfma(-u, q, x), y, q);
+  return tfma(tfma(-u, q, x), y, q);
+}
+
+// The way to the next face of one axis (hi: the upper one), from the
+// compensated position (FP32: p + pe); infinite along the axis's planes.
+template <typename T>
+__device__ __forceinline__ T face_way(T lo, T d, int v, bool hi, T p, T pe, T u, T y) {
+  const T face = lo + T(v + (hi ? 1 : 0)) * d;
+  const T t = tmax(div_by((face - p) - pe, u, y), T(0));
+  return tabs(u) < T(1e-30) ? tinf<T>() : t;
+}
+
+// Moves of the voxel walk, one after the other until kDueMin / 64 of the live
+// lanes are due for the rest of the loop: each to the exit face of the
+// packet's voxel v or to the interaction point (pk.state = kInteract),
+// whichever is nearer, tallying the piece.  A face where the region changes
+// or the grid ends is left to voxel_face (pk.state = kSurface, the face in
+// pk.links).  Called with every lane of the wave active.
+//
+// What bounds it is the chain of one move -- three divisions, the region of
+// the next voxel from memory, the tally -- and, with the card full, their
+// instructions.  So the reciprocals are kept for as long as the direction is,
+// the next voxel's region is asked for before the piece is tallied, and
+// the tally is the SDF walk's, with no lane-by-lane staging.  1e6 packets of
+// the voxelised cylinder (256^3) 45.3 to 37.6 ms, 1e5 15.5 to 10.9, a lone
+// packet's move 1.31 to 0.85 us.  (A fifth wave per SIMD: no faster; bricks
+// for its tally: 38.1 against 37.6.)
 template <typename T, bool TRACE>
-__device__ bool voxel_step(JobRef a, Regions<T> rg, Packet<T>& pk, int v[3], Lane& ln, LdsTallies& L, int max_steps,
-                           uint32_t max_events) {
-  ScP sc = kptr(a.sc);
-  if (++pk.steps > max_steps || pk.k > max_events) {
-    atomicAdd(&L.sum[kSStalled], pk.w);
-    atomicAdd(&L.cnt[kCStalls], 1ull);
-    record<T, TRACE>(a, pk, ln, SMCRT_EV_STALL);
-    return false;
-  }
-  ++ln.n_steps;
-  T texit = tinf<T>();
-  int ax = 0;
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const T ui = comp(pk.u, i);
-    if (ui == T(0)) continue;
-    const T face = Tab<T>::g_lo(sc, i) + T(v[i] + (ui > T(0) ? 1 : 0)) * Tab<T>::g_d(sc, i);
-    // from the compensated position (FP32: p + pe)
-    const T t = tmax(((face - comp(pk.p, i)) - comp(pk.pe, i)) / ui, T(0));
-    if (t < texit) {
-      texit = t;
-      ax = i;
+__device__ __forceinline__ void voxel_moves(JobRef a, Packet<T>& pk, int v[3], Lane& ln, WaveTally& wt, LdsTallies& L,
+                                            int lane, int n_live, int due_min, int most, int max_steps,
+                                            uint32_t max_events) {
+  uint64_t on = __ballot(pk.state == kTransport);
+  if (on == 0ull) return;
+  ScP sc = fresh(kptr(a.sc));
+  const int nx = sc->g_dims[0], ny = sc->g_dims[1], nz = sc->g_dims[2];
+  const V3<T> u = pk.u, y = mk(T(1) / u.x, T(1) / u.y, T(1) / u.z);
+  const bool ux = u.x > T(0), uy = u.y > T(0), uz = u.z > T(0);
+  int idx = vox_index(sc, v);
+  do {
+    bool go = pk.state == kTransport;
+    if (go) {
+      if (++pk.steps > max_steps || pk.k > max_events) {
+        atomicAdd(&L.sum[kSStalled], pk.w);
+        atomicAdd(&L.cnt[kCStalls], 1ull);
+        record<T, TRACE>(a, pk, ln, SMCRT_EV_STALL);
+        pk.state = kDead;
+        go = false;
+      }
     }
-  }
-  const int idx = vox_index(sc, v);
-  const T s = pk.mut > T(0) ? (T)(pk.tau * (double)pk.inv_mut) : tinf<T>();
-  if (s <= texit) {  // interaction inside this voxel
-    if (a.fluence != nullptr && s > T(0)) run_add(a.fluence, ln, idx, pk.w * (double)s);
-    shift(pk, s);
-    pk.tau = 0.0;
-    pk.state = kInteract;
-    return true;
-  }
-  if (a.fluence != nullptr && texit > T(0)) run_add(a.fluence, ln, idx, pk.w * (double)texit);
-  shift(pk, texit);
-  pk.tau -= (double)pk.mut * (double)texit;
-  const T ua = comp(pk.u, ax);
+    T len = T(0);
+    int r2 = -1, face = 0, step = 0, dir = 0;
+    bool inter = false;
+    if (go) {
+      ++ln.n_steps;
+      const T tx = face_way(Tab<T>::g_lo(sc, 0), Tab<T>::g_d(sc, 0), v[0], ux, pk.p.x, pk.pe.x, u.x, y.x);
+      const T ty = face_way(Tab<T>::g_lo(sc, 1), Tab<T>::g_d(sc, 1), v[1], uy, pk.p.y, pk.pe.y, u.y, y.y);
+      const T tz = face_way(Tab<T>::g_lo(sc, 2), Tab<T>::g_d(sc, 2), v[2], uz, pk.p.z, pk.pe.z, u.z, y.z);
+      const bool bx = tx <= ty && tx <= tz, by = !bx && ty <= tz;  // (ties: x before y before z)
+      const T texit = bx ? tx : (by ? ty : tz);
+      const bool up = bx ? ux : (by ? uy : uz);
+      const int va = bx ? v[0] : (by ? v[1] : v[2]), na = bx ? nx : (by ? ny : nz);
+      dir = up ? 1 : -1;
+      face = (bx ? 0 : (by ? 2 : 4)) + (up ? 1 : 0);
+      step = (bx ? 1 : (by ? nx : nx * ny)) * dir;
+      if (va != (up ? na - 1 : 0)) r2 = (int)a.vox[idx + step];
+      const T s = pk.mut > T(0) ? (T)(pk.tau * (double)pk.inv_mut) : tinf<T>();
+      inter = s <= texit;
+      len = inter ? s : texit;
+      shift(pk, len);
+      pk.tau = inter ? 0.0 : pk.tau - (double)pk.mut * (double)len;
+    }
+    if (a.fluence != nullptr) {
+      run_piece<true>(a.fluence, *ln.stage, wt, ln.run, go && len > T(0), idx, pk.w * (double)len);
+      tally_drain(a.fluence, *ln.stage, wt, kDrain, lane);
+    }
+    if (go) {
+      const bool stay = !inter && r2 == pk.region;
+      idx += stay ? step : 0;
+      v[0] += stay && face < 2 ? dir : 0;
+      v[1] += stay && (face >> 1) == 1 ? dir : 0;
+      v[2] += stay && face >= 4 ? dir : 0;
+      pk.links = face;
+      pk.state = inter ? kInteract : (stay ? kTransport : kSurface);
+    }
+    on = __ballot(pk.state == kTransport);
+  } while (on != 0ull && (n_live - __popcll(on)) * 64 < due_min * n_live && --most > 0);
+}
+
+// A packet on face pk.links of its voxel v, where the region changes or the
+// grid ends.  Returns false when the packet has ended (escape).
+template <typename T, bool TRACE>
+__device__ bool voxel_face(JobRef a, Regions<T> rg, Packet<T>& pk, int v[3], Lane& ln, LdsTallies& L) {
+  ScP sc = kptr(a.sc);
+  const int face = pk.links, ax = face >> 1;
   int w2[3] = {v[0], v[1], v[2]};
-  w2[ax] += ua > T(0) ? 1 : -1;
-  const int face = 2 * ax + (ua > T(0) ? 1 : 0);
+  w2[ax] += (face & 1) ? 1 : -1;
   const bool off = w2[ax] < 0 || w2[ax] >= sc->g_dims[ax];
   const int r2 = off ? sc->n_regions : (int)a.vox[vox_index(sc, w2)];
   const double n1 = rg[pk.region].n, n2 = rg[r2].n;

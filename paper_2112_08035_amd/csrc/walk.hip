@@ -28,6 +28,8 @@
 // full-wave FP64 atomics.
 #include <hip/hip_runtime.h>
 
+#include <climits>
+
 #include "launch.h"
 #include "voxel_model.h"
 #include "walk_common.h"
@@ -316,7 +318,6 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
   LdsTallies& L = Lw[wib];
   RegionRow<T>* rows = Rw[STAGE ? 0 : wib];
   const Regions<T> rg = (Regions<T>)rows;
-  if (lane == 0) Sw[wib].n = 0;
   clear_tallies(L, lane);
 
   Lane ln;
@@ -325,7 +326,7 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
   ln.run.sum = 0.0;
   ln.abs_sum = 0.0;
   ln.abs_region = -1;
-  ln.n_steps = ln.n_inter = ln.n_pieces = ln.n_atomics = 0;
+  ln.n_steps = ln.n_inter = 0;
   ln.rec = nullptr;
   ln.n_rec = 0;
   WaveTally wt = {0, 0ull, 0ull};
@@ -462,9 +463,10 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
         continue;
       }
 
-      // ---- one voxel move (voxelised model)
+      // ---- moves from voxel to voxel (voxelised model)
       if constexpr (GEOM == kGeomVoxel) {
-        if (pk.state == kTransport && !voxel_step<T, TRACE>(a, rg, pk, vx, ln, L, max_steps, max_events)) pk.state = kDead;
+        voxel_moves<T, TRACE>(a, pk, vx, ln, wt, L, lane, __popcll(lmask), kDueMin, EPOCH ? 16 : INT_MAX, max_steps, max_events);
+        if (pk.state == kSurface) pk.state = voxel_face<T, TRACE>(a, rg, pk, vx, ln, L) ? kTransport : kDead;
       }
 
       // ---- free-flight reuse: the distance evaluated at the last step's
@@ -689,8 +691,7 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
       // every drained atomic has completed at the L2.  Issued here, they
       // complete while the next iteration's step runs.
       if (a.fluence != nullptr) {
-        if constexpr (GEOM == kGeomSdf) tally_drain(a.fluence, *ln.stage, wt, kDrain, lane);
-        else stage_drain(a.fluence, *ln.stage, kDrain, lane);
+        tally_drain(a.fluence, *ln.stage, wt, kDrain, lane);
       }
     }
 

@@ -1036,7 +1036,6 @@ constexpr int kDrain = 64;   // entries that trigger a drain in the walk loop
 struct WaveStage {
   double val[kStage];
   int v[kStage];
-  int n;
 };
 
 // An interface step of one packet, shared by the lanes of its group (LDS).
@@ -1053,7 +1052,7 @@ struct Lane {
   WaveStage* stage; // this wave's staging area (LDS)
   double abs_sum;   // absorbed weight not yet added to the workgroup sums
   int abs_region;
-  uint32_t n_steps, n_inter, n_pieces, n_atomics;  // (pieces and atomics: the voxel model's)
+  uint32_t n_steps, n_inter;
   // trace
   smcrt_event* rec;
   int n_rec;
@@ -1061,46 +1060,6 @@ struct Lane {
 
 __device__ __forceinline__ void grid_add(double* F, int v, double val) {
   __builtin_amdgcn_global_atomic_fadd_f64((SMCRT_G double*)F + v, val);
-}
-
-// Stages F[v] += val for the lanes active at the call (any subset of the
-// wave); when the stage is full it adds directly.
-__device__ __forceinline__ void stage_add(double* F, WaveStage& S, int v, double val) {
-  const uint64_t m = __ballot(1);
-  const int n = __popcll(m);
-  const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-  const int base = __builtin_amdgcn_readfirstlane(S.n);
-  if (base + n <= kStage) {
-    S.v[base + rank] = v;
-    S.val[base + rank] = val;
-    if (rank == 0) S.n = base + n;
-  } else {
-    grid_add(F, v, val);
-  }
-}
-
-// Adds the staged entries to F once at least min_count are waiting (voxel
-// model).  Called with every lane of the wave active.
-__device__ __forceinline__ void stage_drain(double* F, WaveStage& S, int min_count, int lane) {
-  const int cnt = __builtin_amdgcn_readfirstlane(S.n);
-  if (cnt > 0 && cnt >= min_count) {
-    for (int i = lane; i < cnt; i += 64) grid_add(F, S.v[i], S.val[i]);
-    if (lane == 0) S.n = 0;
-  }
-}
-
-__device__ __forceinline__ void run_add(double* F, Lane& ln, int v, double val) {
-  ++ln.n_pieces;
-  if (v == ln.run.v) {
-    ln.run.sum += val;
-  } else {
-    if (ln.run.v >= 0) {
-      stage_add(F, *ln.stage, ln.run.v, ln.run.sum);
-      ++ln.n_atomics;
-    }
-    ln.run.v = v;
-    ln.run.sum = val;
-  }
 }
 
 // Index of voxel (x, y, z) in a grid of 2x2x2 bricks ((nx+1)/2 by (ny+1)/2
@@ -1422,6 +1381,34 @@ __device__ __forceinline__ int pick(bool c, int a, int b) { return c ? a : b; }
 // 64 runs of 1e5 packets in a batch 41.0 to 38.2 ms, 1e4 packets of the vessel
 // scene 11.5 to 9.7, 1e5 packets of the 50^3 sphere 5.0 to 4.2; 1e7 packets of
 // the slab, bound by the additions themselves, 295 both ways.)
+// Adds val at voxel v to the lane's run, for the lanes with some set: a run
+// that v ends is staged, or added to F where the stage is full.  SAME: v may
+// be the run's own voxel.  Called with every lane of the wave active.
+template <bool SAME>
+__device__ __forceinline__ void run_piece(double* F, WaveStage& S, WaveTally& wt, Run& run, bool some, int v, double val) {
+  const bool same = SAME && v == run.v;
+  const bool push = some && !same && run.v >= 0;
+  const uint64_t ends = __ballot(push);
+  if (ends != 0ull) {
+    const int n = __popcll(ends);
+    if (wt.n + n <= kStage) {
+      const int at = wt.n + __builtin_amdgcn_mbcnt_hi((uint32_t)(ends >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ends, 0u));
+      if (push) {
+        S.v[at] = run.v;
+        S.val[at] = run.sum;
+      }
+      wt.n += n;
+    } else if (push) {
+      grid_add(F, run.v, run.sum);
+    }
+    wt.atomics += (unsigned long long)n;
+  }
+  wt.pieces += (unsigned long long)__popcll(__ballot(some));
+  const double sum = same ? run.sum + val : val;
+  run.sum = some ? sum : run.sum;
+  run.v = some ? v : run.v;
+}
+
 template <typename T, bool BRICK>
 __device__ __forceinline__ void tally_pieces(double* F, WaveStage& S, WaveTally& wt, Run& run, bool active, int lin,
                                              DdaAxis<T> X, DdaAxis<T> Y, DdaAxis<T> Z, int nx, int ny, int nz, T t, T t1,
@@ -1438,28 +1425,8 @@ __device__ __forceinline__ void tally_pieces(double* F, WaveStage& S, WaveTally&
     const T m = tmin(X.tn, tmin(Y.tn, Z.tn)), tn = tmin(m, t1);
     const T len = tn - t;
     const double val = w * (double)len;
-    const bool some = active && len > T(0);
-    const bool same = first && lin == run.v;
-    const bool push = some && !same && run.v >= 0;
-    const uint64_t ends = __ballot(push);
-    if (ends != 0ull) {
-      const int n = __popcll(ends);
-      if (wt.n + n <= kStage) {
-        const int at = wt.n + __builtin_amdgcn_mbcnt_hi((uint32_t)(ends >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ends, 0u));
-        if (push) {
-          S.v[at] = run.v;
-          S.val[at] = run.sum;
-        }
-        wt.n += n;
-      } else if (push) {
-        grid_add(F, run.v, run.sum);
-      }
-      wt.atomics += (unsigned long long)n;
-    }
-    wt.pieces += (unsigned long long)__popcll(__ballot(some));
-    const double sum = same ? run.sum + val : val;
-    run.sum = some ? sum : run.sum;
-    run.v = some ? lin : run.v;
+    if (first) run_piece<true>(F, S, wt, run, active && len > T(0), lin, val);
+    else run_piece<false>(F, S, wt, run, active && len > T(0), lin, val);
     // cross the nearest plane (ties: x before y before z)
     const bool bx = X.tn == m, by = !bx && Y.tn == m, bz = !bx && !by;
     int step = pick(bx, ix, pick(by, iy, iz));
@@ -1727,18 +1694,15 @@ __device__ __forceinline__ void clear_tallies(LdsTallies& L, int lane) {
 // every lane of the wave active.
 __device__ __forceinline__ void flush_wave(JobRef a, Lane& ln, WaveTally& wt, LdsTallies& L, int lane) {
   if (a.fluence != nullptr) {
-    stage_drain(a.fluence, *ln.stage, 1, lane);
     tally_drain(a.fluence, *ln.stage, wt, 1, lane);
   }
   if (ln.run.v >= 0) {
     grid_add(a.fluence, ln.run.v, ln.run.sum);
-    ++ln.n_atomics;
+    atomicAdd(&L.cnt[kCAtomics], 1ull);
   }
   if (ln.abs_region >= 0) atomicAdd(&L.absorbed[ln.abs_region], ln.abs_sum);
   atomicAdd(&L.cnt[kCSteps], (unsigned long long)ln.n_steps);
   atomicAdd(&L.cnt[kCInteractions], (unsigned long long)ln.n_inter);
-  atomicAdd(&L.cnt[kCPieces], (unsigned long long)ln.n_pieces);
-  atomicAdd(&L.cnt[kCAtomics], (unsigned long long)ln.n_atomics);
   if (lane == 0) {
     L.cnt[kCPieces] += wt.pieces;
     L.cnt[kCAtomics] += wt.atomics;
@@ -1748,7 +1712,7 @@ __device__ __forceinline__ void flush_wave(JobRef a, Lane& ln, WaveTally& wt, Ld
   ln.run.sum = 0.0;
   ln.abs_region = -1;
   ln.abs_sum = 0.0;
-  ln.n_steps = ln.n_inter = ln.n_pieces = ln.n_atomics = 0;
+  ln.n_steps = ln.n_inter = 0;
   if (lane == 0) L.cnt[kCEvents] = L.cnt[kCInteractions] + L.cnt[kCInterfaces];
   __threadfence_block();
   // One lane per entry, and none for a zero: waves that found no packet left

@@ -208,3 +208,25 @@ def test_tally_of_rays_along_voxel_planes(S, eng, orc, W, u, precision):
         o, g = orc.run(desc, 3, n), S.run(desc, 3, n, engine=eng, precision=precision)
         eps = 1e-12 if precision == "f64" else 1e-5  # of lengths of size 1, n of them
         assert np.max(np.abs(g["fluence_raw"] - o["fluence_raw"])) <= eps * n, (x, u)
+
+
+@pytest.mark.parametrize("dims", [(1, 1, 1), (3, 1, 2), (17, 33, 5), (64, 64, 64)])
+def test_voxel_moves_over_grid_sizes(S, eng, orc, W, dims):
+    """the voxelised model from one voxel up: traces and counts against the
+    oracle's voxel walk, and the same packets in two launches"""
+    desc = dict(W.cylinder_scene(8), geometry="voxel")
+    desc["grid"] = dict(desc["grid"], dims=list(dims))
+    n = 128
+    mut = [rg["mua"] + rg["mus"] for rg in desc["regions"]]
+    o = [orc.trace(desc, 17, pid, 40, voxel=True) for pid in range(n)]
+    g = S.trace(desc, 17, list(range(n)), 40, engine=eng, precision="f64")
+    frac, worst, bad = compare_traces(o, g, extent_of(S, desc), 1e-6, cap=40, mut=mut)
+    assert frac >= 0.98, (frac, worst, bad[:5])
+    for precision in ("f64", "f32"):
+        a = S.run(desc, 17, 3001, engine=eng, precision=precision)
+        h = [S.run(desc, 17, m, first=f, engine=eng, precision=precision) for f, m in ((0, 1), (1, 3000))]
+        for k in ("events", "steps", "interactions", "voxel_pieces", "escapes"):
+            assert a[k] == sum(x[k] for x in h), k
+        F = sum(x["fluence_raw"] for x in h)
+        assert np.max(np.abs(a["fluence_raw"] - F)) <= 1e-12 * F.max()
+        assert abs(identity_residual(a)) <= 1e-9 * 3001
