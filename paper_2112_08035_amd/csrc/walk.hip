@@ -411,7 +411,17 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
       if constexpr (EPOCH) {
         if (!stop && (++iter & 15) == 0 && __builtin_amdgcn_s_memrealtime() - t0 > B.deadline) stop = true;
         if (stop) {
-          save_live<T>(B, a, pk.state != kDead, pk, vx, lane);
+          // what this kernel's packets have no use for is saved as constants:
+          // held for the save alone, it cost the serving kernels spills (16
+          // requests 120 to 110 ms)
+          int at[3] = {0, 0, 0};
+          if constexpr (GEOM == kGeomVoxel)
+            for (int i = 0; i < 3; ++i) at[i] = vx[i];
+          if constexpr (!kRelax) {
+            pk.pd = T(-1);
+            pk.pl = T(0);
+          }
+          save_live<T>(B, a, pk.state != kDead, pk, at, lane);
           pk.state = kDead;
           exhausted = true;
           break;
@@ -435,7 +445,10 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
             rtake = rb < a.resume_n ? (int)min((unsigned int)ndead, a.resume_n - rb) : 0;
             if (rtake < ndead) resumed_all = true;
             if (open && rank < rtake) {
-              load_saved<T>(a, rb + (unsigned int)rank, pk, vx);
+              int at[3];
+              load_saved<T>(a, rb + (unsigned int)rank, pk, at);
+              if constexpr (GEOM == kGeomVoxel)
+                for (int i = 0; i < 3; ++i) vx[i] = at[i];
             }
           }
           const int rest = ndead - rtake;
