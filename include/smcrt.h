@@ -428,8 +428,9 @@ smcrt_status smcrt_run_batch_ex(smcrt_engine* engine, int n, const smcrt_scene* 
  * hipMalloc): it calls no hipMalloc, hipFree or other allocating routine.
  * Its device scratch -- the scene's tables, the job record, the packet
  * counter, the uniform-grid build buffers and the voxel model's region
- * grid -- lives in a fixed array of 32 MiB that each GPU the library runs
- * on holds from its first use until the process ends; the walk tallies
+ * grid -- lives in a fixed array of 32 MiB (and 12 MiB beside it for the
+ * walk's evaluation records) that each GPU the library runs on holds from
+ * its first use until the process ends; the walk tallies
  * straight into out->fluence_raw (no brick grid), so results equal
  * smcrt_run_ex's up to the order of FP64 sums.  The engine supplies the
  * device and launch options only.  Every call on one GPU shares that GPU's
@@ -438,8 +439,9 @@ smcrt_status smcrt_run_batch_ex(smcrt_engine* engine, int n, const smcrt_scene* 
  * The scene's packed tables are copied from host memory on hip_stream: the
  * scene must not change or be destroyed until that work has completed.
  * Errors: as smcrt_run_ex, and SMCRT_E_INVALID when the scene needs more
- * scratch than 32 MiB (e.g. a voxel-model grid above about 3.3e7 voxels, or
- * tables of about 6e4 primitives); nothing is queued then. */
+ * scratch than 32 MiB, evaluation records aside (e.g. a voxel-model grid
+ * above about 3.3e7 voxels, or tables of about 6e4 primitives); nothing is
+ * queued then. */
 smcrt_status smcrt_run_ex_static(smcrt_engine* engine, const smcrt_scene* scene, uint64_t seed, uint64_t first_packet,
                                  uint64_t n_packets, const smcrt_outputs* out, void* hip_stream);
 

@@ -1280,7 +1280,7 @@ __device__ __forceinline__ void record(JobRef a, const Packet<T>& pk, Lane& ln, 
 
 // Moves the packet len along u.  The tally is deferred: the straight path
 // since the last change of direction collects in pend and is credited to
-// the grid in one pass by flush_tally, which runs before the direction
+// the grid in one pass by tally_path, which runs before the direction
 // changes or the position jumps (interactions, interface events) and when
 // the packet ends.  Collinear sphere-tracing steps thus share one DDA, and
 // the lanes of a wave run it together.
