@@ -1415,24 +1415,33 @@ static smcrt_status launch_jobs(smcrt_engine* e, const std::vector<JobSpec>& job
     return SMCRT_OK;
   };
   if (!e->opts.use_graph || tr || vox_out || dq) return enqueue(st);
-  // replay the captured sequence when the launch shape is the same
-  std::vector<uint64_t> key = {(uint64_t)(uintptr_t)base, image_bytes, total, jobs.size(), (uint64_t)cg[0].block,
+  // Replay the captured sequence when everything its nodes hold as arguments
+  // is the same: addresses, sizes, launch shapes, and the grid dims of the
+  // brick additions.  What kernels read from the uploaded tables may differ.
+  std::vector<uint64_t> key = {(uint64_t)(uintptr_t)base, jobs_off, counters_off, image_bytes, total, jobs.size(),
                                (uint64_t)e->opts.precision, (uint64_t)B.refill_min, (uint64_t)B.surface_min};
   for (int g = 0; g < kLaunchClasses; ++g) {
     key.push_back((uint64_t)cg[g].grid);
+    key.push_back((uint64_t)cg[g].block);
     key.push_back((uint64_t)has_geom[g]);
   }
   for (size_t j = 0; j < jobs.size(); ++j) {
+    const SceneHeader* h = reinterpret_cast<const SceneHeader*>(uniq[job_scene[j]]->blob.data());
+    key.push_back((uint64_t)job_scene[j]);
     key.push_back(brick_off[j]);
     key.push_back(brick_n[j]);
+    for (int i = 0; i < 3; ++i) key.push_back((uint64_t)h->g_dims[i]);
     key.push_back((uint64_t)(uintptr_t)jobs[j].fluence);
   }
   for (size_t u = 0; u < uniq.size(); ++u) {
-    const Accel& A = reinterpret_cast<const SceneHeader*>(uniq[u]->blob.data())->acc;
+    const SceneHeader* h = reinterpret_cast<const SceneHeader*>(uniq[u]->blob.data());
+    const Accel& A = h->acc;
     key.push_back(blob_off[u]);
+    key.push_back(h->prim_offset_d);
     key.push_back((uint64_t)A.region);
     key.push_back((uint64_t)A.n_prims);
     key.push_back((uint64_t)A.n_cells);
+    key.push_back(acc_off[u]);
     key.push_back(vox_off[u]);
     key.push_back(vox_n[u]);
   }
