@@ -1871,16 +1871,35 @@ static double server_now(const smcrt_server* sv) {
   return std::chrono::duration<double>(std::chrono::steady_clock::now() - sv->t0).count();
 }
 
-// device bytes a request holds while admitted: its outputs, its scene
-// tables, the grid buffers of its accelerated region and its voxel grid
-// (served requests tally straight into their output grid: no brick grid).
-// The walk's evaluation records are not charged to it.
+// A resident request's device allocation: the scene's whole blob, the
+// accelerated region's grid buffers, the voxel model's region grid.
+struct SlotLayout {
+  size_t acc_off = 0, acc_cb = 0, vox_off = 0, vox_n = 0, bytes = 0;
+};
+static SlotLayout slot_layout(const smcrt_scene* s) {
+  const SceneHeader* h = reinterpret_cast<const SceneHeader*>(s->blob.data());
+  SlotLayout l;
+  l.bytes = align256(s->blob.size());
+  if (h->acc.region >= 0) {
+    l.acc_cb = align256(sizeof(uint32_t) * ((size_t)h->acc.n_cells + 1));
+    l.acc_off = l.bytes;
+    l.bytes += 3 * l.acc_cb + align256(sizeof(uint32_t) * h->acc.capacity);
+  }
+  if (h->geometry == kGeomVoxel) {
+    l.vox_n = (size_t)h->g_dims[0] * h->g_dims[1] * h->g_dims[2];
+    l.vox_off = l.bytes;
+    l.bytes = align256(l.bytes + l.vox_n);
+  }
+  return l;
+}
+
+// device bytes a request holds while admitted: its allocation, its outputs
+// and its job record (served requests tally straight into their output grid:
+// no brick grid)
 static uint64_t request_footprint(const smcrt_scene* s) {
   const SceneHeader* h = reinterpret_cast<const SceneHeader*>(s->blob.data());
-  uint64_t b = h->table_bytes + sizeof(WalkArgs) - 2 * sizeof(void*) + sizeof(smcrt_tallies) + 8 * kMaxRegions + 256;
+  uint64_t b = slot_layout(s).bytes + sizeof(WalkArgs) + sizeof(smcrt_tallies) + 8 * kMaxRegions;
   if (h->has_grid) b += 8ull * h->g_dims[0] * h->g_dims[1] * h->g_dims[2];
-  if (h->acc.region >= 0) b += 12ull * ((uint64_t)h->acc.n_cells + 1) + 4ull * h->acc.capacity + 3 * 256;
-  if (h->geometry == kGeomVoxel) b += (uint64_t)h->g_dims[0] * h->g_dims[1] * h->g_dims[2] + 256;
   return b;
 }
 
@@ -1964,12 +1983,10 @@ namespace {
 
 constexpr int kMaxSlots = 128;
 
-// a resident request and its device allocation: scene tables, the
-// accelerated region's grid buffers, the voxel model's region grid
-struct Slot {
+// a resident request and its device allocation
+struct Slot : SlotLayout {
   Request* r = nullptr;
   char* dev = nullptr;
-  size_t acc_off = 0, acc_cb = 0, vox_off = 0, vox_n = 0;
   uint64_t handed = 0;     // packet ids handed out so far
   uint32_t saved = 0;      // packets in flight at the end of the last epoch
   bool draining = false;   // left with packets saved (cancelled): idle for one epoch before reuse
@@ -2106,19 +2123,8 @@ static smcrt_status resident_admit(smcrt_server* sv, int s, Request* r) {
   Resident* R = sv->res;
   Slot& sl = R->slots[s];
   const SceneHeader* h = reinterpret_cast<const SceneHeader*>(r->scene->blob.data());
-  size_t off = align256(r->scene->blob.size());
-  sl.acc_off = sl.acc_cb = sl.vox_off = sl.vox_n = 0;
-  if (h->acc.region >= 0) {
-    sl.acc_cb = align256(sizeof(uint32_t) * ((size_t)h->acc.n_cells + 1));
-    sl.acc_off = off;
-    off += 3 * sl.acc_cb + align256(sizeof(uint32_t) * h->acc.capacity);
-  }
-  if (h->geometry == kGeomVoxel) {
-    sl.vox_n = (size_t)h->g_dims[0] * h->g_dims[1] * h->g_dims[2];
-    sl.vox_off = off;
-    off = align256(off + sl.vox_n);
-  }
-  HIP_TRY(hipMalloc(&sl.dev, off), "hipMalloc(request tables)");
+  static_cast<SlotLayout&>(sl) = slot_layout(r->scene);
+  HIP_TRY(hipMalloc(&sl.dev, sl.bytes), "hipMalloc(request tables)");
   sl.r = r;
   sl.handed = 0;
   sl.saved = 0;
