@@ -68,21 +68,24 @@ __device__ __forceinline__ V3<double> to_d(V3<T> a) { return {(double)a.x, (doub
 template <typename T>
 __device__ __forceinline__ V3<T> from_d(V3<double> a) { return {(T)a.x, (T)a.y, (T)a.z}; }
 
-// Correctly rounded like sqrtf from 2^-96 up: the instruction's result (1 ulp)
-// or a neighbour, by the signs of the residuals.  sqrtf also scales its
-// operand against underflow of the residual and picks out 0 and infinity,
-// which here come through the comparisons as they are.  Below 2^-96 (lengths
-// under 4e-15) the result may be 1 ulp off, and a denormal operand gives
-// nearly zero.  9 instructions for 16, on the chain of every step: 1e5 packets
-// of the 50^3 sphere 3.86 to 3.69 ms, 1e6 of the reflectance image 20.2 to
-// 19.4, 1e4 of the vessel scene 9.5 to 9.0, 2e5 of the gallery 49.9 to 48.2.
+// Correctly rounded, as sqrtf is, by the steps the compiler takes for it on
+// this target: the instruction's result (1 ulp) or a neighbour, by the signs
+// of the residuals, from an operand scaled up where its residual would
+// underflow.  sqrtf also picks out 0 and infinity, which here come through the
+// comparisons as they are.  14 instructions for 16, on the chain of every
+// step: 1e6 packets of the reflectance image 20.1 to 19.7 ms, 1e3 of the 50^3
+// sphere 1.06 to 1.04.  (Without the scaling 19.3 and 1.03 ms, but denormal
+// operands, of lengths under 1e-19, gave nearly zero.)
 __device__ __forceinline__ float tsqrt(float x) {
 #if defined(__HIP_DEVICE_COMPILE__)
+  const bool small = x < 0x1p-96f;
+  x = __builtin_ldexpf(x, small ? 64 : 0);
   const float s = __builtin_amdgcn_sqrtf(x);
   const float lo = __builtin_bit_cast(float, __builtin_bit_cast(int, s) - 1);
   const float hi = __builtin_bit_cast(float, __builtin_bit_cast(int, s) + 1);
-  const float r = __builtin_fmaf(-lo, s, x) <= 0.0f ? lo : s;
-  return __builtin_fmaf(-hi, s, x) > 0.0f ? hi : r;
+  const float q = __builtin_fmaf(-lo, s, x) <= 0.0f ? lo : s;
+  const float r = __builtin_fmaf(-hi, s, x) > 0.0f ? hi : q;
+  return __builtin_ldexpf(r, small ? -32 : 0);
 #else
   return __builtin_sqrtf(x);
 #endif
