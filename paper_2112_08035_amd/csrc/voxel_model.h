@@ -153,21 +153,32 @@ __device__ bool enter_grid(JobRef a, Regions<T> rg, Packet<T>& pk, int v[3], Lan
 }
 
 // x / u, y = 1 / u: corrections of x y by its residual (Markstein), the last
-// steps of a division without its own reciprocal
+// steps of a division without its own reciprocal.  Not for |u| < kSteep, where
+// y and x y may overflow.  (FP32: an |x| under 2^-102 has a residual that
+// underflows, and a quotient that may be 1 ulp off.)
 template <typename T>
 __device__ __forceinline__ T div_by(T x, T u, T y) {
   T q = x * y;
   q = tfma(tfma(-u, q, x), y, q);
   return tfma(tfma(-u, q, x), y, q);
 }
-
-// The way to the next face of one axis (hi: the upper one), from the
-// compensated position (FP32: p + pe); infinite along the axis's planes.
+constexpr double kSteep = 0x1p-40;
 template <typename T>
-__device__ __forceinline__ T face_way(T lo, T d, int v, bool hi, T p, T pe, T u, T y) {
+__device__ __forceinline__ bool steep(T u) {
+  return u != T(0) && tabs(u) < T(kSteep);
+}
+
+// The gap to the next face of one axis (hi: the upper one), from the
+// compensated position (FP32: p + pe).
+template <typename T>
+__device__ __forceinline__ T face_gap(T lo, T d, int v, bool hi, T p, T pe) {
   const T face = lo + T(v + (hi ? 1 : 0)) * d;
-  const T t = tmax(div_by((face - p) - pe, u, y), T(0));
-  return tabs(u) < T(1e-30) ? tinf<T>() : t;
+  return (face - p) - pe;
+}
+// The way there, from its quotient by u; infinite along the axis's planes.
+template <typename T>
+__device__ __forceinline__ T face_way(T q, T u) {
+  return u == T(0) ? tinf<T>() : tmax(q, T(0));
 }
 
 // Moves of the voxel walk, one after the other until kDueMin / 64 of the live
@@ -195,6 +206,8 @@ __device__ __forceinline__ void voxel_moves(JobRef a, Packet<T>& pk, int v[3], L
   const int nx = sc->g_dims[0], ny = sc->g_dims[1], nz = sc->g_dims[2];
   const V3<T> u = pk.u, y = mk(T(1) / u.x, T(1) / u.y, T(1) / u.z);
   const bool ux = u.x > T(0), uy = u.y > T(0), uz = u.z > T(0);
+  // (one scalar branch a move: the divisions themselves are rare)
+  const bool any_steep = __ballot(pk.state == kTransport && (steep(u.x) || steep(u.y) || steep(u.z))) != 0ull;
   int idx = vox_index(sc, v);
   do {
     bool go = pk.state == kTransport;
@@ -212,9 +225,16 @@ __device__ __forceinline__ void voxel_moves(JobRef a, Packet<T>& pk, int v[3], L
     bool inter = false;
     if (go) {
       ++ln.n_steps;
-      const T tx = face_way(Tab<T>::g_lo(sc, 0), Tab<T>::g_d(sc, 0), v[0], ux, pk.p.x, pk.pe.x, u.x, y.x);
-      const T ty = face_way(Tab<T>::g_lo(sc, 1), Tab<T>::g_d(sc, 1), v[1], uy, pk.p.y, pk.pe.y, u.y, y.y);
-      const T tz = face_way(Tab<T>::g_lo(sc, 2), Tab<T>::g_d(sc, 2), v[2], uz, pk.p.z, pk.pe.z, u.z, y.z);
+      const T hx = face_gap(Tab<T>::g_lo(sc, 0), Tab<T>::g_d(sc, 0), v[0], ux, pk.p.x, pk.pe.x);
+      const T hy = face_gap(Tab<T>::g_lo(sc, 1), Tab<T>::g_d(sc, 1), v[1], uy, pk.p.y, pk.pe.y);
+      const T hz = face_gap(Tab<T>::g_lo(sc, 2), Tab<T>::g_d(sc, 2), v[2], uz, pk.p.z, pk.pe.z);
+      T qx = div_by(hx, u.x, y.x), qy = div_by(hy, u.y, y.y), qz = div_by(hz, u.z, y.z);
+      if (any_steep) {
+        if (steep(u.x)) qx = hx / u.x;
+        if (steep(u.y)) qy = hy / u.y;
+        if (steep(u.z)) qz = hz / u.z;
+      }
+      const T tx = face_way(qx, u.x), ty = face_way(qy, u.y), tz = face_way(qz, u.z);
       const bool bx = tx <= ty && tx <= tz, by = !bx && ty <= tz;  // (ties: x before y before z)
       const T texit = bx ? tx : (by ? ty : tz);
       const bool up = bx ? ux : (by ? uy : uz);
