@@ -186,7 +186,8 @@ __device__ __forceinline__ T face_way(T q, T u) {
 // packet's voxel v or to the interaction point (pk.state = kInteract),
 // whichever is nearer, tallying the piece.  A face where the region changes
 // or the grid ends is left to voxel_face (pk.state = kSurface, the face in
-// pk.links).  Called with every lane of the wave active.
+// pk.links).  Takes at most `most` moves and returns how many, the last one
+// aside.  Called with every lane of the wave active.
 //
 // What bounds it is the chain of one move -- three divisions, the region of
 // the next voxel from memory, the tally -- and, with the card full, their
@@ -197,11 +198,12 @@ __device__ __forceinline__ T face_way(T q, T u) {
 // packet's move 1.31 to 0.85 us.  (A fifth wave per SIMD: no faster; bricks
 // for its tally: 38.1 against 37.6.)
 template <typename T, bool TRACE>
-__device__ __forceinline__ void voxel_moves(JobRef a, Packet<T>& pk, int v[3], Lane& ln, WaveTally& wt, LdsTallies& L,
+__device__ __forceinline__ int voxel_moves(JobRef a, Packet<T>& pk, int v[3], Lane& ln, WaveTally& wt, LdsTallies& L,
                                             int lane, int n_live, int due_min, int most, int max_steps,
                                             uint32_t max_events) {
   uint64_t on = __ballot(pk.state == kTransport);
-  if (on == 0ull) return;
+  if (on == 0ull) return 0;
+  int left = most;
   ScP sc = fresh(kptr(a.sc));
   const int nx = sc->g_dims[0], ny = sc->g_dims[1], nz = sc->g_dims[2];
   const V3<T> u = pk.u, y = mk(T(1) / u.x, T(1) / u.y, T(1) / u.z);
@@ -263,7 +265,8 @@ __device__ __forceinline__ void voxel_moves(JobRef a, Packet<T>& pk, int v[3], L
       pk.state = inter ? kInteract : (stay ? kTransport : kSurface);
     }
     on = __ballot(pk.state == kTransport);
-  } while (on != 0ull && (n_live - __popcll(on)) * 64 < due_min * n_live && --most > 0);
+  } while (on != 0ull && (n_live - __popcll(on)) * 64 < due_min * n_live && --left > 0);
+  return most - left;
 }
 
 // A packet on face pk.links of its voxel v, where the region changes or the
