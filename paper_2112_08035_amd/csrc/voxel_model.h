@@ -152,33 +152,22 @@ __device__ bool enter_grid(JobRef a, Regions<T> rg, Packet<T>& pk, int v[3], Lan
   return false;
 }
 
-// x / u, y = 1 / u: corrections of x y by its residual (Markstein), the last
-// steps of a division without its own reciprocal.  Not for |u| < kSteep, where
-// y and x y may overflow.  (FP32: an |x| under 2^-102 has a residual that
-// underflows, and a quotient that may be 1 ulp off.)
+// The way to the next face of one axis (hi: the upper one), from the
+// compensated position (FP32: p + pe): the gap by u, y = 1 / u, as corrections
+// of the product by its residual (Markstein), the last steps of a division
+// without its own reciprocal.  Infinite along the axis's planes (u = 0), and
+// where the product is: from there on the residual overflows, and no scene is
+// as large.  (FP32: a gap under 2^-102 has a residual that underflows, and a
+// quotient that may be 1 ulp off; a |u| under 2^-128 has no reciprocal and
+// crosses only the faces it stands on.)
 template <typename T>
-__device__ __forceinline__ T div_by(T x, T u, T y) {
-  T q = x * y;
-  q = tfma(tfma(-u, q, x), y, q);
-  return tfma(tfma(-u, q, x), y, q);
-}
-constexpr double kSteep = 0x1p-40;
-template <typename T>
-__device__ __forceinline__ bool steep(T u) {
-  return u != T(0) && tabs(u) < T(kSteep);
-}
-
-// The gap to the next face of one axis (hi: the upper one), from the
-// compensated position (FP32: p + pe).
-template <typename T>
-__device__ __forceinline__ T face_gap(T lo, T d, int v, bool hi, T p, T pe) {
+__device__ __forceinline__ T face_way(T lo, T d, int v, bool hi, T p, T pe, T u, T y) {
+  constexpr T kFar = sizeof(T) == 4 ? T(0x1p100) : T(0x1p1000);
   const T face = lo + T(v + (hi ? 1 : 0)) * d;
-  return (face - p) - pe;
-}
-// The way there, from its quotient by u; infinite along the axis's planes.
-template <typename T>
-__device__ __forceinline__ T face_way(T q, T u) {
-  return u == T(0) ? tinf<T>() : tmax(q, T(0));
+  const T x = (face - p) - pe, q0 = x * y;
+  T q = tfma(tfma(-u, q0, x), y, q0);
+  q = tfma(tfma(-u, q, x), y, q);
+  return u == T(0) || q0 >= kFar ? tinf<T>() : tmax(q, T(0));  // (behind the face by rounding: 0)
 }
 
 // Moves of the voxel walk, one after the other until kDueMin / 64 of the live
@@ -194,13 +183,14 @@ __device__ __forceinline__ T face_way(T q, T u) {
 // instructions.  So the reciprocals are kept for as long as the direction is,
 // the next voxel's region is asked for before the piece is tallied, and
 // the tally is the SDF walk's, with no lane-by-lane staging.  1e6 packets of
-// the voxelised cylinder (256^3) 45.3 to 37.6 ms, 1e5 15.5 to 10.9, a lone
+// the voxelised cylinder (256^3) 45.0 to 36.7 ms, 1e5 15.5 to 10.9, a lone
 // packet's move 1.31 to 0.85 us.  (A fifth wave per SIMD: no faster; bricks
-// for its tally: 38.1 against 37.6.)
+// for its tally: 38.1 against 37.6; true divisions where a component is small,
+// behind a branch or in a loop of their own, 1 and 2 % slower.)
 template <typename T, bool TRACE>
 __device__ __forceinline__ int voxel_moves(JobRef a, Packet<T>& pk, int v[3], Lane& ln, WaveTally& wt, LdsTallies& L,
-                                            int lane, int n_live, int due_min, int most, int max_steps,
-                                            uint32_t max_events) {
+                                           int lane, int n_live, int due_min, int most, int max_steps,
+                                           uint32_t max_events) {
   uint64_t on = __ballot(pk.state == kTransport);
   if (on == 0ull) return 0;
   int left = most;
@@ -208,8 +198,6 @@ __device__ __forceinline__ int voxel_moves(JobRef a, Packet<T>& pk, int v[3], La
   const int nx = sc->g_dims[0], ny = sc->g_dims[1], nz = sc->g_dims[2];
   const V3<T> u = pk.u, y = mk(T(1) / u.x, T(1) / u.y, T(1) / u.z);
   const bool ux = u.x > T(0), uy = u.y > T(0), uz = u.z > T(0);
-  // (one scalar branch a move: the divisions themselves are rare)
-  const bool any_steep = __ballot(pk.state == kTransport && (steep(u.x) || steep(u.y) || steep(u.z))) != 0ull;
   int idx = vox_index(sc, v);
   do {
     bool go = pk.state == kTransport;
@@ -227,16 +215,9 @@ __device__ __forceinline__ int voxel_moves(JobRef a, Packet<T>& pk, int v[3], La
     bool inter = false;
     if (go) {
       ++ln.n_steps;
-      const T hx = face_gap(Tab<T>::g_lo(sc, 0), Tab<T>::g_d(sc, 0), v[0], ux, pk.p.x, pk.pe.x);
-      const T hy = face_gap(Tab<T>::g_lo(sc, 1), Tab<T>::g_d(sc, 1), v[1], uy, pk.p.y, pk.pe.y);
-      const T hz = face_gap(Tab<T>::g_lo(sc, 2), Tab<T>::g_d(sc, 2), v[2], uz, pk.p.z, pk.pe.z);
-      T qx = div_by(hx, u.x, y.x), qy = div_by(hy, u.y, y.y), qz = div_by(hz, u.z, y.z);
-      if (any_steep) {
-        if (steep(u.x)) qx = hx / u.x;
-        if (steep(u.y)) qy = hy / u.y;
-        if (steep(u.z)) qz = hz / u.z;
-      }
-      const T tx = face_way(qx, u.x), ty = face_way(qy, u.y), tz = face_way(qz, u.z);
+      const T tx = face_way(Tab<T>::g_lo(sc, 0), Tab<T>::g_d(sc, 0), v[0], ux, pk.p.x, pk.pe.x, u.x, y.x);
+      const T ty = face_way(Tab<T>::g_lo(sc, 1), Tab<T>::g_d(sc, 1), v[1], uy, pk.p.y, pk.pe.y, u.y, y.y);
+      const T tz = face_way(Tab<T>::g_lo(sc, 2), Tab<T>::g_d(sc, 2), v[2], uz, pk.p.z, pk.pe.z, u.z, y.z);
       const bool bx = tx <= ty && tx <= tz, by = !bx && ty <= tz;  // (ties: x before y before z)
       const T texit = bx ? tx : (by ? ty : tz);
       const bool up = bx ? ux : (by ? uy : uz);
