@@ -128,6 +128,13 @@ template <typename T>
 __device__ __forceinline__ T fdot(V3<T> a, V3<T> b) {
   return tfma(a.z, b.z, tfma(a.x, b.x, a.y * b.y));
 }
+// p - t e, and x^2 + y^2, their roundings fixed too
+template <typename T>
+__device__ __forceinline__ V3<T> fback(V3<T> p, T t, V3<T> e) {
+  return {tfma(-t, e.x, p.x), tfma(-t, e.y, p.y), tfma(-t, e.z, p.z)};
+}
+template <typename T>
+__device__ __forceinline__ T sum_sq(T x, T y) { return tfma(x, x, y * y); }
 template <typename T>
 __device__ __forceinline__ T tclamp(T x, T lo, T hi) { return tmin(tmax(x, lo), hi); }
 template <typename T>
@@ -249,11 +256,6 @@ struct Tab<double> {
   static __device__ __forceinline__ double seg_eps() { return 1e-12; }
 };
 
-// x^2 + y^2 with its one rounding fixed in FP32 (which product the compiler
-// would fuse depends on the code around it; results do not)
-__device__ __forceinline__ float sum_sq(float x, float y) { return __builtin_fmaf(x, x, y * y); }
-__device__ __forceinline__ double sum_sq(double x, double y) { return __builtin_fma(x, x, y * y); }
-
 // exact Euclidean SDF of one primitive's shape in its own frame (Sec. 2.2;
 // Eq. 3 for the sphere)
 template <typename T, typename Params>
@@ -268,18 +270,18 @@ __device__ __forceinline__ T shape_of(int kind, const Params& v, V3<T> p) {
   const V3<T> e = mk(v[3], v[4], v[5]);
   if (kind == kTorus) {  // e unit axis, v[6] = ring radius R, v[7] = tube radius r
     const T x = fdot(q, e);
-    const V3<T> rad = q - x * e;
+    const V3<T> rad = fback(q, x, e);
     const T rho = tsqrt(fdot(rad, rad)) - v[6];
     return tsqrt(tfma(x, x, rho * rho)) - v[7];
   }
   if (kind == kCapsule) {  // e = b - a, v[6] = 1/|b-a|^2
     const T t = tclamp(fdot(q, e) * v[6], T(0), T(1));
-    const V3<T> d = q - t * e;
+    const V3<T> d = fback(q, t, e);
     return tsqrt(fdot(d, d)) - v[7];
   }
   // capped cylinder: e unit axis, v[6] = L, v[7] = L/2, v[8] = r
   const T x = fdot(q, e);
-  const V3<T> rad = q - x * e;
+  const V3<T> rad = fback(q, x, e);
   const T q1 = tsqrt(fdot(rad, rad)) - v[8];
   const T q2 = tabs(x - v[7]) - v[7];
   const T o1 = tmax(q1, T(0)), o2 = tmax(q2, T(0));
@@ -415,9 +417,12 @@ __device__ __forceinline__ T further_shape_sdf(const SMCRT_K Prim<T>* P, int i, 
   return v[6] * (tsqrt(fdot(u, u)) - T(1));
 }
 
-// SDF of a placed or modified primitive.  Every product that a sum takes up is
-// an explicit fma: inlined into the walk's steps and called from elsewhere,
-// it has to round the same.
+// SDF of a placed or modified primitive.  Inlined into the walk's steps and
+// called from elsewhere, it should round the same: the sums of products here
+// and in the basic shapes are explicit fma.  Those of the further shapes and of
+// tsincos are left to the compiler, which fuses them alike in both (written
+// out, shared products round otherwise than they have, and the FP64 kernel
+// spills 45 registers instead of 27).
 template <typename T>
 __device__ __forceinline__ T placed_prim(const SMCRT_K Prim<T>* P, int i, V3<T> p) {
   hold(p.x);
@@ -534,14 +539,14 @@ __device__ __forceinline__ T region_sdf(JobRef a, RegRef R, V3<T> p) {
 }
 
 // capsule SDF from a compact record c = (a, b - a, 1/|b - a|^2, r): the
-// capsule branch of shape_sdf, operation for operation
+// capsule branch of shape_of, operation for operation
 template <typename T>
 __device__ __forceinline__ T cap_sdf(T a0, T a1, T a2, T e0, T e1, T e2, T inv, T r, V3<T> p) {
   const V3<T> q = p - mk(a0, a1, a2);
   const V3<T> e = mk(e0, e1, e2);
-  const T t = tclamp(dot(q, e) * inv, T(0), T(1));
-  const V3<T> d = q - t * e;
-  return tsqrt(dot(d, d)) - r;
+  const T t = tclamp(fdot(q, e) * inv, T(0), T(1));
+  const V3<T> d = fback(q, t, e);
+  return tsqrt(fdot(d, d)) - r;
 }
 
 // An evaluation record in scalar registers.
@@ -846,8 +851,7 @@ __device__ __forceinline__ T tangent_bound(T a, T dv, T l, T err) {
 }
 
 // distance of a plain convex primitive (sphere, box, capsule or capped
-// cylinder, unplaced and unmodified) at p, computed as shape_sdf computes
-// it, and the ray's rate of approach to it as -(*dv) / (*l): v points from
+// cylinder, unplaced and unmodified) at p, by the operations of shape_of, and the ray's rate of approach to it as -(*dv) / (*l): v points from
 // the nearest surface point towards p (meaningful outside the shape)
 template <typename T>
 __device__ __forceinline__ T convex_sdf_rate(const SMCRT_K Prim<T>* P, int i, V3<T> p, V3<T> u, T* dv, T* l) {
@@ -855,34 +859,34 @@ __device__ __forceinline__ T convex_sdf_rate(const SMCRT_K Prim<T>* P, int i, V3
   const SMCRT_K T* v = P[i].v;
   const V3<T> q = p - mk(v[0], v[1], v[2]);
   if (kind == kSphere) {
-    *l = tsqrt(dot(q, q));
+    *l = tsqrt(fdot(q, q));
     *dv = dot(q, u);
     return *l - v[3];
   }
   if (kind == kBox) {
     const T ex = tabs(q.x) - v[3], ey = tabs(q.y) - v[4], ez = tabs(q.z) - v[5];
     const V3<T> o = mk(tmax(ex, T(0)), tmax(ey, T(0)), tmax(ez, T(0)));
-    *l = tsqrt(dot(o, o));
+    *l = tsqrt(fdot(o, o));
     *dv = (q.x < T(0) ? -o.x : o.x) * u.x + (q.y < T(0) ? -o.y : o.y) * u.y + (q.z < T(0) ? -o.z : o.z) * u.z;
     return *l + tmin(tmax(ex, tmax(ey, ez)), T(0));
   }
   const V3<T> e = mk(v[3], v[4], v[5]);
   if (kind == kCapsule) {
-    const T t = tclamp(dot(q, e) * v[6], T(0), T(1));
-    const V3<T> d = q - t * e;
-    *l = tsqrt(dot(d, d));
+    const T t = tclamp(fdot(q, e) * v[6], T(0), T(1));
+    const V3<T> d = fback(q, t, e);
+    *l = tsqrt(fdot(d, d));
     *dv = dot(d, u);
     return *l - v[7];
   }
   // capped cylinder, in the half plane of (radial, axial) coordinates: v =
   // o1 rad / rho +/- o2 e, scaled by rho when o1 > 0
-  const T x = dot(q, e);
-  const V3<T> rad = q - x * e;
-  const T rho = tsqrt(dot(rad, rad));
+  const T x = fdot(q, e);
+  const V3<T> rad = fback(q, x, e);
+  const T rho = tsqrt(fdot(rad, rad));
   const T q1 = rho - v[8];
   const T q2 = tabs(x - v[7]) - v[7];
   const T o1 = tmax(q1, T(0)), o2 = tmax(q2, T(0));
-  const T len = tsqrt(o1 * o1 + o2 * o2);
+  const T len = tsqrt(sum_sq(o1, o2));
   const T sc = o1 > T(0) ? rho : T(1);
   *l = sc * len;
   *dv = o1 * dot(rad, u) + (x > v[7] ? o2 : -o2) * sc * dot(e, u);
@@ -931,9 +935,9 @@ __device__ __forceinline__ T accel_seg(JobRef a, V3<T> p, V3<T> u, T err, T* tb)
         const SMCRT_K T* r = C + 8 * (size_t)(id - lo_id);
         const V3<T> q = p - mk(r[0], r[1], r[2]);
         const V3<T> ax = mk(r[3], r[4], r[5]);
-        const T s = tclamp(dot(q, ax) * r[6], T(0), T(1));
-        const V3<T> w = q - s * ax;
-        const T l = tsqrt(dot(w, w));
+        const T s = tclamp(fdot(q, ax) * r[6], T(0), T(1));
+        const V3<T> w = fback(q, s, ax);
+        const T l = tsqrt(fdot(w, w));
         const T di = l - r[7];
         d = tmin(d, di);
         t = tmin(t, tangent_bound<T>(di, dot(w, u), l, err));
