@@ -1397,8 +1397,9 @@ static smcrt_status launch_jobs(smcrt_engine* e, const std::vector<JobSpec>& job
     }
     if (vox_out) return SMCRT_OK;
     if (dq) {
-      const bool placed = reinterpret_cast<const SceneHeader*>(uniq[job_scene[0]]->blob.data())->xf != 0;
-      HIP_TRY(launch_distance(e->opts.precision, B.jobs, 0, dq->points, dq->n, dq->accelerated, placed, dq->dist, dq->owner,
+      const SceneHeader* h = reinterpret_cast<const SceneHeader*>(uniq[job_scene[0]]->blob.data());
+      const bool singly = h->xf != 0 || h->n_prims <= h->n_regions;
+      HIP_TRY(launch_distance(e->opts.precision, B.jobs, 0, dq->points, dq->n, dq->accelerated, singly, dq->dist, dq->owner,
                               dq->normals, q),
               "distance kernel");
       return SMCRT_OK;

@@ -99,12 +99,14 @@ __device__ __forceinline__ void region_sdf_n(JobRef a, RegRef R, const V3<T> (&p
 // fill the card so (two waves per SIMD).  With a lane doing one evaluation
 // after the other, each waiting for its own loads, the vessel scene's FP64
 // distances and normals took, in ms, 7.56 (1e3 points), 7.59 (1e5) and 14.9
-// (3e5); split 0.88, 2.5 and 7.0; with kNormals 2.9, 3.5 and 7.0.  1e6 points
-// of the 50^3 sphere 0.042, split 0.056, kNormals 0.043.
-// kNormalsPlaced: placed primitives share no loads between two points, and
-// the pair's registers cost a wave per SIMD: 1e6 points of the gallery scene
-// 0.297 so, 0.307 with kNormals, 0.335 split (2e5: 0.098, 0.101, 0.092).
-enum PointsMode { kDistances, kNormals, kNormalsPlaced, kNormalsSplit };
+// (3e5); split 0.88, 2.5 and 7.0; with kNormals 2.9, 3.5 and 7.0.
+// kNormalsSingly: one evaluation after the other, the distances of all regions
+// first.  Placed primitives share no loads between two points, and the pair's
+// registers cost a wave per SIMD: 1e6 points of the gallery scene 0.297 so,
+// 0.307 with kNormals, 0.335 split.  Where no region has a second primitive,
+// none is read ahead: 1e6 points of the 50^3 sphere 0.029 so, 0.031 with
+// kNormals, 0.043 split, of the three-layer slab 0.064, 0.071 and 0.076.
+enum PointsMode { kDistances, kNormals, kNormalsSingly, kNormalsSplit };
 
 // region r at x + h and x - h on the given axis: the difference
 __device__ __forceinline__ double axis_difference(JobRef a, int r, bool grid, int axis, V3<double> x, double h) {
@@ -153,7 +155,7 @@ distance_kernel(const WalkArgs* __restrict__ job_table, int job, const double* _
         const V3<T> p[1] = {mk((T)q.x, (T)q.y, (T)q.z)};
         T d[1];
         if (grid) d[0] = accel_sdf<T, true>(a, grid_of<T>(sc->acc), p[0]);
-        else if constexpr (MODE == kNormalsPlaced) d[0] = region_sdf<T, true>(a, sc->reg[r], p[0]);
+        else if constexpr (MODE == kNormalsSingly) d[0] = region_sdf<T, true>(a, sc->reg[r], p[0]);
         else region_sdf_n<T, 1, MODE == kDistances>(a, sc->reg[r], p, d);
         if (i < n) dist[i * (uint64_t)nr + r] = (double)d[0];
         if (d[0] < T(0)) own = r;
@@ -168,14 +170,6 @@ distance_kernel(const WalkArgs* __restrict__ job_table, int job, const double* _
           else g[2] = v;
         }
         if (i < n) store_normal(out, g[0], g[1], g[2]);
-      } else if constexpr (MODE == kNormalsPlaced) {
-        auto f = [&](double x, double y, double z) {
-          return grid ? accel_sdf<double, true>(a, grid_of<double>(sc->acc), mk(x, y, z))
-                      : region_sdf<double, true>(a, sc->reg[r], mk(x, y, z));
-        };
-        if (i < n)
-          store_normal(out, f(q.x + h, q.y, q.z) - f(q.x - h, q.y, q.z), f(q.x, q.y + h, q.z) - f(q.x, q.y - h, q.z),
-                       f(q.x, q.y, q.z + h) - f(q.x, q.y, q.z - h));
       } else if constexpr (kSplit) {
         if (wave != 0) diff[r & 1][wave - 1][lane] = axis_difference(a, r, grid, wave - 1, q, h);
         __syncthreads();
@@ -183,28 +177,43 @@ distance_kernel(const WalkArgs* __restrict__ job_table, int job, const double* _
       }
     }
     if (owner && i < n && (!kSplit || wave == 0)) owner[i] = own;
+    if constexpr (MODE == kNormalsSingly) {
+      for (int r = 0; r < nr; ++r) {
+        const bool grid = accelerated && r == a.acc_region;
+        auto f = [&](double x, double y, double z) {
+          return grid ? accel_sdf<double, true>(a, grid_of<double>(sc->acc), mk(x, y, z))
+                      : region_sdf<double, true>(a, sc->reg[r], mk(x, y, z));
+        };
+        if (i < n)
+          store_normal(normals + 3 * (i * (uint64_t)nr + r), f(q.x + h, q.y, q.z) - f(q.x - h, q.y, q.z),
+                       f(q.x, q.y + h, q.z) - f(q.x, q.y - h, q.z), f(q.x, q.y, q.z + h) - f(q.x, q.y, q.z - h));
+      }
+    }
     if constexpr (kSplit) __syncthreads();
   }
 }
 
 template <typename T>
 static void launch_distance_kernel(const WalkArgs* d_jobs, int job, const double* points, uint64_t n, int accelerated,
-                                   bool placed, double* dist, int32_t* owner, double* normals, hipStream_t stream) {
-  constexpr uint64_t kSplitBelow = 131072;  // two waves per SIMD with a point per lane
+                                   bool singly, double* dist, int32_t* owner, double* normals, hipStream_t stream) {
+  // two waves per SIMD with a point per lane.  us split and not, at 1e5, 2e5
+  // and 1e6 points: gallery 49 and 63, 76 and 81, 273 and 262; 20 capsules 53
+  // and 66, 75 and 84, 234 and 239; slab 21.6 and 22.7, 27.5 and 25.6, 75 and 64
+  constexpr uint64_t kSplitBelow = 131072;
   const bool split = normals && n < kSplitBelow;
   uint64_t blocks = split ? (n + 63) / 64 : (n + 255) / 256;
   if (blocks > 16384) blocks = 16384;
   auto k = distance_kernel<T, kDistances>;
-  if (normals) k = split ? distance_kernel<T, kNormalsSplit> : (placed ? distance_kernel<T, kNormalsPlaced> : distance_kernel<T, kNormals>);
+  if (normals) k = split ? distance_kernel<T, kNormalsSplit> : (singly ? distance_kernel<T, kNormalsSingly> : distance_kernel<T, kNormals>);
   hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, stream, d_jobs, job, points, n, accelerated, dist, owner,
                      normals);
 }
 
 hipError_t launch_distance(int precision, const WalkArgs* d_jobs, int job, const double* points, uint64_t n, int accelerated,
-                           bool placed, double* dist, int32_t* owner, double* normals, hipStream_t stream) {
+                           bool singly, double* dist, int32_t* owner, double* normals, hipStream_t stream) {
   if (!d_jobs || !points || !dist || job < 0 || n == 0) return hipErrorInvalidValue;
-  if (precision == 1) launch_distance_kernel<double>(d_jobs, job, points, n, accelerated, placed, dist, owner, normals, stream);
-  else launch_distance_kernel<float>(d_jobs, job, points, n, accelerated, placed, dist, owner, normals, stream);
+  if (precision == 1) launch_distance_kernel<double>(d_jobs, job, points, n, accelerated, singly, dist, owner, normals, stream);
+  else launch_distance_kernel<float>(d_jobs, job, points, n, accelerated, singly, dist, owner, normals, stream);
   return hipGetLastError();
 }
 
