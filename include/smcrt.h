@@ -300,9 +300,10 @@ enum { SMCRT_PREC_F32 = 0, SMCRT_PREC_F64 = 1 };
  * stay FP64); F64 runs the whole walk in FP64.  block: threads per workgroup
  * (64, 128, 192 or 256).  blocks_per_cu: resident workgroups per CU the
  * grid is sized for (1..32; 0 = as many as fit).  refill_min: dead lanes a wave waits for
- * before it emits new packets (1..64).  surface_min: lanes a wave gathers at
- * surfaces before it runs the FP64 interface step (1..64).  Results do not
- * depend on any of these except precision. */
+ * before it emits new packets (1..64; a wave without packets does not wait).
+ * surface_min: a wave runs the FP64 interface step once surface_min 64ths of
+ * its packets wait at surfaces (1..64).  Results do not depend on any of these
+ * except precision. */
 typedef struct {
   int32_t precision;
   int32_t block;

@@ -1173,10 +1173,11 @@ static LaunchCfg launch_cfg(smcrt_engine* e, int launch_class) {
 // all of them when there are packets for every lane, else the packets are
 // spread over all waves.  A short launch ends with its longest packet, and a
 // wave's iteration is as long as the paths of all its lanes together: 1e3
-// packets of the 50^3 sphere take 2.1 ms one to a wave and 3.6 ms in 16 full
-// waves, 1e5 packets 7.3 ms against 7.9 ms.  A quarter of these lanes (so
-// that most waves' lanes are refilled four times) was 8 % slower on 5e5
-// packets of a vessel network, twice as many the same to 7 % slower.
+// packets of the 50^3 sphere take 1.08 ms one to a wave and 2.12 in 16 full
+// waves, 1e4 of a vessel network 11.9 and 17.4, 1e5 of the sphere 3.8 and 3.9,
+// 1e5 of the network 69 to 70 both ways.  Half of these lanes are the same (3.6
+// on 1e5 of the sphere), twice as many 10 % slower on 1e4 of the network.  (A
+// wave with fewer of them than refill_min emits again when all are dead.)
 static int32_t packet_lanes(const LaunchCfg& cfg, uint64_t n) {
   const uint64_t waves = (uint64_t)cfg.grid * (uint64_t)(cfg.block / 64);
   const uint64_t each = n / waves + (n % waves != 0);

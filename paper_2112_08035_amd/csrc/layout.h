@@ -202,7 +202,7 @@ struct LaunchCfg {
   int block;          // threads per workgroup
   int grid;           // workgroups
   int refill_min;     // dead lanes gathered before a wave emits
-  int surface_min;    // lanes gathered before a wave runs the interface step
+  int surface_min;    // 64ths of a wave's packets gathered before it runs the interface step
 };
 
 // Per-run device arguments of the walk kernel.

@@ -15,10 +15,10 @@
 // tallies are FP64 in both.  Steps may be over-relaxed (a multiple of the
 // surface distance, checked at the next evaluation; Sec. 5).
 //
-// Divergence control: lanes that reach a surface wait until surface_min
-// lanes of the wave are there (or nothing else can move), so the long FP64
-// interface step runs with many lanes on; dead lanes wait for refill_min
-// before a wave emits.
+// Divergence control: packets that reach a surface wait until surface_min / 64
+// of the wave's packets are there, and the wave then takes up to eight of them
+// through the long FP64 interface step together, eight lanes each; dead lanes
+// wait for refill_min (or for a wave without packets) before a wave emits.
 //
 // Tally: a lane keeps the straight path since its last tally pending and
 // credits it through the voxel grid (a register-only DDA) before an
@@ -46,10 +46,10 @@ namespace smcrt {
 // each central difference side by side -- four evaluations in a row instead
 // of 2 n_regions + 12 -- through one copy of the SDF code (40 KB of kernel
 // instead of 200 KB, which the instruction cache does not hold).  Every SDF
-// is the one the packet's own lane would compute.  Measured against each lane
-// doing its own: 5e5 packets of a 2000-capsule network 126 to 95 ms, 1e6 of
-// the 256^3 cylinder 37.3 to 34.8 ms, 1e7 of the slab unchanged (its
-// interface steps are a small share and its tally atomics bound it).
+// is the one the packet's own lane would compute.  Against each lane doing its
+// own: 5e5 packets of a 2000-capsule network 25 % less time, 1e6 of the 256^3
+// cylinder 7 %, 1e7 of the slab the same (its interface steps are a small
+// share and its tally atomics bound it).
 
 // value of lane k of the caller's group of eight
 __device__ __forceinline__ double group_get(double x, int group, int k) {
@@ -415,8 +415,8 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
         }
         if (stop) {
           // what this kernel's packets have no use for is saved as constants:
-          // held for the save alone, it cost the serving kernels spills (16
-          // requests 120 to 110 ms)
+          // held for the save alone, it cost the serving kernels spills and 16
+          // requests 8 % of their time
           int at[3] = {0, 0, 0};
           if constexpr (GEOM == kGeomVoxel)
             for (int i = 0; i < 3; ++i) at[i] = vx[i];
@@ -464,7 +464,7 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
               const uint64_t id = base + (uint64_t)(rank - rtake);
               if (id < a.n) {
                 pk.pid = a.first + id;
-                  emit<T, TRACE, XF>(a, rg, pk, ln, L);
+                emit<T, TRACE, XF>(a, rg, pk, ln, L);
                 if constexpr (GEOM == kGeomVoxel) {
                   if (!enter_grid<T, TRACE>(a, rg, pk, vx, ln, L)) pk.state = kDead;
                 }
@@ -513,10 +513,10 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
       // A wave with few packets left thereby takes step after step without
       // passing through it; the longest packets graze surfaces for thousands
       // of steps, and a short launch lasts as long as they do.  64 runs of
-      // 1e5 packets in a batch: the rest of the loop after every step 45.9
-      // ms, as soon as one lane is due 38.2, a quarter 37.6, half 32.0, two
-      // thirds 31.6; 1e5 packets of the 50^3 sphere 7.0, 4.24, -, 3.94, -;
-      // 1e7 of the slab 295.2 (one lane) and 294.2 (half).
+      // 1e5 packets in a batch: as soon as one lane is due 35.2 ms, a quarter
+      // 33.2, half 30.4, two thirds 30.3; 1e5 packets of the 50^3 sphere 4.0,
+      // 3.9, 3.8, 4.0; 1e7 of the slab 305 all ways.  (The rest of the loop
+      // after every step cost the batch 20 % more, the sphere 65 %.)
       uint64_t on = GEOM == kGeomSdf ? __ballot(pk.state == kTransport) : 0ull;
       if (on != 0ull) {
         const ScP hot = fresh(sc);
@@ -734,7 +734,7 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
       caps_lds = (LdsCaps)caps_fill;
       if (!stage_caps(jobs[cur], caps_fill)) caps_lds = nullptr;
       fill_regions<T>(jobs[cur], rows, threadIdx.x, blockDim.x);
-        __syncthreads();
+      __syncthreads();
     } else {
       // job drained by this wave (or the epoch ended): hand in its sums,
       // take the next job

@@ -482,9 +482,9 @@ __device__ __forceinline__ T placed_prim(const SMCRT_K Prim<T>* P, int i, V3<T> 
 // The same as a function, for the rarer places.  UNI: i is the same for every
 // lane.  A function's arguments arrive in vector registers; taken back to
 // scalar ones, the parameters are scalar loads instead of vector loads that
-// wait for the wave's atomics (2e5 packets of the gallery scene 67.6 to 52
-// ms, and to 49 ms with the steps' evaluations inlined; inlined everywhere
-// 50.5 ms).
+// wait for the wave's atomics: 2e5 packets of the gallery scene 23 % less
+// time, with the steps' evaluations inlined 6 % less again, inlined everywhere
+// 3 % more.
 template <typename T, bool UNI>
 __device__ __attribute__((noinline)) T placed_prim_sdf(const SMCRT_K Prim<T>* P, int i, V3<T> p) {
   if constexpr (UNI) {
@@ -710,7 +710,7 @@ __device__ __forceinline__ T region_dist(JobRef a, int r, V3<T> p, LdsCaps lds =
 // then its parameters, that is four or five waits in a row per region.  A
 // record holds all of it in whole cache lines, and the next one is on its way
 // while this one is worked on.  (With the packets' region rows in LDS: 1e5
-// packets of the 50^3 sphere 7.6 to 7.0 ms.)
+// packets of the 50^3 sphere 8 % less time.)
 template <typename T, bool XF>
 __device__ __forceinline__ T walk_distance(JobRef a, const SMCRT_K StepRec<T>* rec, int n_steps, V3<T> p,
                                            LdsCaps lds) {
@@ -1370,24 +1370,6 @@ __device__ __forceinline__ void tally_drain(double* F, WaveStage& S, WaveTally& 
 // picks one of their addresses, which keeps them in memory)
 __device__ __forceinline__ int pick(bool c, int a, int b) { return c ? a : b; }
 
-// Path-length estimator (Sec. 3.1): weight * length of the packet's pending
-// straight path, which ends at its position, credited to every voxel it
-// crosses, by a 3-D DDA in voxel units.  Voxel i spans [lo + i*D, lo +
-// (i+1)*D); indices are clamped on entry and the walk stops when it steps off
-// the grid.  Called with every lane of the wave active; the lanes with want
-// set credit their paths together.
-//
-// A crossing is some forty vector instructions, and what bounds the tally is
-// the wave's wait for its longest path, so the loop is one straight body for
-// all lanes: no lane mask but a flag, the axes in named registers, the voxel
-// index stepped by the axis stride, and the number of staged entries in a
-// scalar register (ends of runs take their places in the stage by a ballot;
-// read from LDS at each run, it was a chain of two LDS accesses per piece).
-// Consecutive pieces of one path are in different voxels: only the first can
-// continue the lane's run.  (With the walk's steps in one straight body too:
-// 64 runs of 1e5 packets in a batch 41.0 to 38.2 ms, 1e4 packets of the vessel
-// scene 11.5 to 9.7, 1e5 packets of the 50^3 sphere 5.0 to 4.2; 1e7 packets of
-// the slab, bound by the additions themselves, 295 both ways.)
 // Adds val at voxel v to the lane's run, for the lanes with some set: a run
 // that v ends is staged, or added to F where the stage is full.  SAME: v may
 // be the run's own voxel.  Called with every lane of the wave active.
@@ -1416,6 +1398,17 @@ __device__ __forceinline__ void run_piece(double* F, WaveStage& S, WaveTally& wt
   run.v = some ? v : run.v;
 }
 
+// The pieces of the lanes' paths, from t to t1.  A crossing is some forty
+// vector instructions, and what bounds the tally is the wave's wait for its
+// longest path, so the loop is one straight body for all lanes: no lane mask
+// but a flag, the axes in named registers, the voxel index stepped by the axis
+// stride, and the number of staged entries in a scalar register (ends of runs
+// take their places in the stage by a ballot; read from LDS at each run, it
+// was a chain of two LDS accesses per piece).  Consecutive pieces of one path
+// are in different voxels: only the first can continue the lane's run.  (With
+// the walk's steps in one straight body too: 64 runs of 1e5 packets in a batch
+// 7 % less time, 1e4 packets of the vessel scene and 1e5 of the 50^3 sphere
+// 16 %; 1e7 of the slab, bound by the additions themselves, the same.)
 template <typename T, bool BRICK>
 __device__ __forceinline__ void tally_pieces(double* F, WaveStage& S, WaveTally& wt, Run& run, bool active, int lin,
                                              DdaAxis<T> X, DdaAxis<T> Y, DdaAxis<T> Z, int nx, int ny, int nz, T t, T t1,
@@ -1455,6 +1448,12 @@ __device__ __forceinline__ void tally_pieces(double* F, WaveStage& S, WaveTally&
   while (__ballot(active) != 0ull) piece(false);
 }
 
+// Path-length estimator (Sec. 3.1): weight * length of the packet's pending
+// straight path, which ends at its position, credited to every voxel it
+// crosses, by a 3-D DDA in voxel units.  Voxel i spans [lo + i*D, lo +
+// (i+1)*D); indices are clamped on entry and the walk stops when it steps off
+// the grid.  Called with every lane of the wave active; the lanes with want
+// set credit their paths together.
 template <typename T>
 __device__ __forceinline__ void tally_path(JobRef a, const Packet<T>& pk, bool want, Lane& ln, WaveTally& wt) {
   if (a.fluence == nullptr || __ballot(want) == 0ull) return;
@@ -1462,9 +1461,8 @@ __device__ __forceinline__ void tally_path(JobRef a, const Packet<T>& pk, bool w
   const int nx = sc->g_dims[0], ny = sc->g_dims[1], nz = sc->g_dims[2];
   // One straight block, the lanes' conditions selected: nested branches cost
   // an exec mask and the zeros of some fourteen results each.  (1e3 packets of
-  // the 50^3 sphere 1.13 to 1.01 ms, 64 runs of 1e5 31.5 to 29.8, 1e6 of the
-  // cylinder 33.3 to 31.8, 2e5 of the gallery 48.1 to 46.3; 1e7 of the slab
-  // 303 to 299.)
+  // the 50^3 sphere 11 % less time, 64 runs of 1e5 5 %, 1e6 of the cylinder and
+  // 2e5 of the gallery 4 %, 1e7 of the slab 1 %.)
   const V3<T> inv = Tab<T>::g_inv(sc);
   const V3<T> lo = Tab<T>::g_lo(sc);
   const T len = pk.pend;
@@ -1725,7 +1723,7 @@ __device__ __forceinline__ void flush_wave(JobRef a, Lane& ln, WaveTally& wt, Ld
   // One lane per entry, and none for a zero: waves that found no packet left
   // have only zeros, and the additions of all waves to one cache line queue
   // up behind each other.  (Lane 0 adding every entry in turn: a launch of
-  // one packet of the 50^3 sphere 0.50 ms, so 0.14; 1e3 packets 1.41 and 1.15.)
+  // one packet of the 50^3 sphere 0.36 ms more, of 1e3 0.26.)
   if (a.absorbed != nullptr && lane < a.sc->n_regions && L.absorbed[lane] != 0.0)
     unsafeAtomicAdd(a.absorbed + lane, L.absorbed[lane]);
   if (a.tallies != nullptr) {
