@@ -175,8 +175,7 @@ __device__ __forceinline__ T face_way(T lo, T d, int v, bool hi, T p, T pe, T u,
 // packet's voxel v or to the interaction point (pk.state = kInteract),
 // whichever is nearer, tallying the piece.  A face where the region changes
 // or the grid ends is left to voxel_face (pk.state = kSurface, the face in
-// pk.links).  Takes at most `most` moves and returns how many, the last one
-// aside.  Called with every lane of the wave active.
+// pk.links).  At most `most` moves.  Called with every lane of the wave active.
 //
 // What bounds it is the chain of one move -- three divisions, the region of
 // the next voxel from memory, the tally -- and, with the card full, their
@@ -188,12 +187,11 @@ __device__ __forceinline__ T face_way(T lo, T d, int v, bool hi, T p, T pe, T u,
 // for its tally: 38.1 against 37.6; true divisions where a component is small,
 // behind a branch or in a loop of their own, 1 and 2 % slower.)
 template <typename T, bool TRACE>
-__device__ __forceinline__ int voxel_moves(JobRef a, Packet<T>& pk, int v[3], Lane& ln, WaveTally& wt, LdsTallies& L,
-                                           int lane, int n_live, int due_min, int most, int max_steps,
-                                           uint32_t max_events) {
+__device__ __forceinline__ void voxel_moves(JobRef a, Packet<T>& pk, int v[3], Lane& ln, WaveTally& wt, LdsTallies& L,
+                                            int lane, int n_live, int due_min, int most, int max_steps,
+                                            uint32_t max_events) {
   uint64_t on = __ballot(pk.state == kTransport);
-  if (on == 0ull) return 0;
-  int left = most;
+  if (on == 0ull) return;
   ScP sc = fresh(kptr(a.sc));
   const int nx = sc->g_dims[0], ny = sc->g_dims[1], nz = sc->g_dims[2];
   const V3<T> u = pk.u, y = mk(T(1) / u.x, T(1) / u.y, T(1) / u.z);
@@ -246,8 +244,7 @@ __device__ __forceinline__ int voxel_moves(JobRef a, Packet<T>& pk, int v[3], La
       pk.state = inter ? kInteract : (stay ? kTransport : kSurface);
     }
     on = __ballot(pk.state == kTransport);
-  } while (on != 0ull && (n_live - __popcll(on)) * 64 < due_min * n_live && --left > 0);
-  return most - left;
+  } while (on != 0ull && (n_live - __popcll(on)) * 64 < due_min * n_live && --most > 0);
 }
 
 // A packet on face pk.links of its voxel v, where the region changes or the

@@ -337,7 +337,6 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
   // in flight for the next epoch
   uint64_t t0 = 0;
   bool stop = false;
-  int since = 0;  // wave uniform: steps since the clock was last read
   if constexpr (EPOCH && !STAGE) t0 = __builtin_amdgcn_s_memrealtime();
 
   // First jobs, XCD-aware: workgroups go to the 8 XCDs in turn (block b to
@@ -409,10 +408,9 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
     for (;;) {
       // ---- end of a resident-serving epoch: save the packets in flight
       if constexpr (EPOCH) {
-        if (!stop && ++since > 16) {
-          since = 0;
-          if (__builtin_amdgcn_s_memrealtime() - t0 > B.deadline) stop = true;
-        }
+        // (an iteration takes up to 16 steps; a counter of steps between the
+        // readings of the clock cost as much as the readings)
+        if (!stop && __builtin_amdgcn_s_memrealtime() - t0 > B.deadline) stop = true;
         if (stop) {
           // what this kernel's packets have no use for is saved as constants:
           // held for the save alone, it cost the serving kernels spills and 16
@@ -481,8 +479,7 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
 
       // ---- moves from voxel to voxel (voxelised model)
       if constexpr (GEOM == kGeomVoxel) {
-        const int moves = voxel_moves<T, TRACE>(a, pk, vx, ln, wt, L, lane, __popcll(lmask), kDueMin, EPOCH ? 16 : INT_MAX, max_steps, max_events);
-        if constexpr (EPOCH) since += moves;
+        voxel_moves<T, TRACE>(a, pk, vx, ln, wt, L, lane, __popcll(lmask), kDueMin, EPOCH ? 16 : INT_MAX, max_steps, max_events);
         if (pk.state == kSurface) pk.state = voxel_face<T, TRACE>(a, rg, pk, vx, ln, L) ? kTransport : kDead;
       }
 
@@ -652,7 +649,6 @@ walk_kernel(const WalkArgs* __restrict__ job_table, BatchArgs B) {
             break;
           // (resident serving: back to the deadline every 16 steps)
         } while (!EPOCH || ++inner < 16);
-        if constexpr (EPOCH) since += inner;
       }
 
       // ---- interface steps, gathered: up to eight packets an iteration,
